@@ -9,12 +9,15 @@
 // or as bf16 at b = 16 (§2.2: a b = 16 GQA layer is the uncompressed cache).
 // The layout written is the one documented in include/kvk.h.
 //
-// One workgroup of 256 threads writes one 32-token block of one stream: it stages
-// the block's K and V in LDS as fp32 (16-byte loads), computes the group metadata
-// with several threads per group and lane reductions, then every thread assembles
-// whole 32-bit words of codes so that the global stores are coalesced.  The kernel
-// is specialised per head width, bit-width and scheme, so that the layout address
-// arithmetic reduces to shifts and masks.
+// One wave writes one 32-token block of one stream at d_h 128, two at d_h 64 (half a
+// wave each), without barriers.  Lane (q, tg) holds channels 8q .. 8q+7 of the eight
+// tokens 16 (n/4) + 4 tg + n%4, n = 0..7: its loads are 16 bytes and a row's lanes
+// read it whole, the 8 channels of a token are a chunk of the K layout and the 8
+// tokens of a channel a chunk of the V layout, so every code word is formed in one
+// lane's registers.  Group minima and maxima are in-lane trees finished by lane
+// swaps.  The block is put together in the wave's LDS slot, in its output order, and
+// leaves with 16-byte stores of contiguous kilobytes.  The kernel is specialised per
+// head width, bit-width, scheme and input type.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -50,340 +53,597 @@ struct CompressArgs {
   // sequences seq_of[0 .. n_seq), whose regions start seq_region[j] bytes after
   // `region`; the inputs stay indexed by the batch's sequence.  n_seq = 0: one table.
   int32_t n_seq, Hkv;
+  int32_t n_streams;  // of the launch
   int32_t seq_of[kWriteSeqs];
   int64_t seq_region[kWriteSeqs];
 };
 
 #pragma clang fp contract(off)
 
-__device__ __forceinline__ uint32_t kivi_code(float x, float s, float z, float levels) {
-  if (s == 0.0f) return 0u;
-  const float t = (x - z) / s;  // IEEE fp32, correctly rounded
-  const float r = fminf(fmaxf(rintf(t), 0.0f), levels);
-  return (uint32_t)r;
-}
+// ---------------------------------------------------------------------------
+// The lanes of a block and their rows
+// ---------------------------------------------------------------------------
 
-__device__ __forceinline__ uint32_t sym_code(float x, float s, int bits) {
-  const float q = (float)((1 << (bits - 1)) - 1);
-  float r = 0.0f;
-  if (s != 0.0f) r = fminf(fmaxf(rintf(x / s), -q), q);
-  return (uint32_t)((int)r + (1 << (bits - 1)));
-}
+template <int D>
+struct Lanes {
+  static constexpr int kQ = D / 8;              // lanes of a row
+  static constexpr int kPerBlock = 4 * kQ;      // lanes of a block: the wave, or half of it
+  static constexpr int kBlocks = 64 / kPerBlock;  // blocks of a wave
+};
 
-// Stage the 32 tokens of a block (K and V, fp32) in LDS: thread (token t, chunk q)
-// moves channels 8q .. 8q+7 with 16-byte loads; tokens past ntok are zero.
-template <int D, int LD>
-__device__ __forceinline__ void stage_block(const CompressArgs& a, int stream, int tok0, int ntok, float* Ks,
-                                            float* Vs, int tid) {
-  constexpr int NQ = D / 8, TPP = 256 / NQ;  // chunks per row, tokens per pass
-  const int q = tid % NQ;
-  for (int t = tid / NQ; t < 32; t += TPP) {
-    f4 k0 = {0.f, 0.f, 0.f, 0.f}, k1 = k0, v0 = k0, v1 = k0;
-    if (t < ntok) {
-      int pos = tok0 + t;
-      if (a.keep) {
-        pos = a.keep[(int64_t)stream * a.n_stored + pos];
-        pos = pos < 0 ? 0 : (pos >= a.n_tokens ? a.n_tokens - 1 : pos);
-      }
-      const int64_t e = ((int64_t)stream * a.n_tokens + pos) * D + 8 * q;
-      if (a.in_f32) {
-        const f4* kp = reinterpret_cast<const f4*>(static_cast<const float*>(a.k) + e);
-        const f4* vp = reinterpret_cast<const f4*>(static_cast<const float*>(a.v) + e);
-        k0 = kp[0], k1 = kp[1], v0 = vp[0], v1 = vp[1];
-      } else {
-        const u4v kw = *reinterpret_cast<const u4v*>(static_cast<const uint16_t*>(a.k) + e);
-        const u4v vw = *reinterpret_cast<const u4v*>(static_cast<const uint16_t*>(a.v) + e);
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-          k0[2 * p] = __uint_as_float(kw[p] << 16), k0[2 * p + 1] = __uint_as_float(kw[p] & 0xffff0000u);
-          k1[2 * p] = __uint_as_float(kw[p + 2] << 16), k1[2 * p + 1] = __uint_as_float(kw[p + 2] & 0xffff0000u);
-          v0[2 * p] = __uint_as_float(vw[p] << 16), v0[2 * p + 1] = __uint_as_float(vw[p] & 0xffff0000u);
-          v1[2 * p] = __uint_as_float(vw[p + 2] << 16), v1[2 * p + 1] = __uint_as_float(vw[p + 2] & 0xffff0000u);
-        }
-      }
-    }
-    *reinterpret_cast<f4*>(&Ks[t * LD + 8 * q]) = k0;
-    *reinterpret_cast<f4*>(&Ks[t * LD + 8 * q + 4]) = k1;
-    *reinterpret_cast<f4*>(&Vs[t * LD + 8 * q]) = v0;
-    *reinterpret_cast<f4*>(&Vs[t * LD + 8 * q + 4]) = v1;
-  }
-}
-
-// bf16 block: 16-byte chunks of 8 values (see the bf16 block layout).
-template <int D, int LD>
-__device__ __forceinline__ void write_bf16_block(const float* Ks, const float* Vs, uint8_t* out, int tid) {
-  uint4* o4 = reinterpret_cast<uint4*>(out);
-  for (int ci = tid; ci < 8 * D; ci += 256) {
-    uint32_t w[4];
-    if (ci < 4 * D) {  // K tile tau: lane shares of D/2 bytes, dealt out in 16-byte pieces
-      const int tau = ci / (2 * D), rem = ci % (2 * D);
-      const int lam = rem & 63, j = rem >> 6;
-      const int t = 16 * tau + (lam & 15), c0 = 32 * j + 8 * (lam >> 4);
-#pragma unroll
-      for (int p = 0; p < 4; ++p)
-        w[p] = (uint32_t)f32_to_bf16_bits(Ks[t * LD + c0 + 2 * p]) |
-               ((uint32_t)f32_to_bf16_bits(Ks[t * LD + c0 + 2 * p + 1]) << 16);
-    } else {
-      const int cv = ci - 4 * D;  // V: lane shares of D bytes
-      const int lam = cv & 63, m = cv >> 6;
-      const int c = 16 * m + (lam & 15), kg = lam >> 4;
-#pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        const int s0 = 2 * p, s1 = 2 * p + 1;
-        const int t0 = 16 * (s0 >> 2) + 4 * kg + (s0 & 3), t1 = 16 * (s1 >> 2) + 4 * kg + (s1 & 3);
-        w[p] = (uint32_t)f32_to_bf16_bits(Vs[t0 * LD + c]) | ((uint32_t)f32_to_bf16_bits(Vs[t1 * LD + c]) << 16);
-      }
-    }
-    o4[ci] = make_uint4(w[0], w[1], w[2], w[3]);
-  }
-}
-
-// The inverse of write_bf16_block: a bf16 block (16-byte loads) into LDS rows as fp32.
-template <int D, int LD>
-__device__ __forceinline__ void stage_bf16_block(const uint8_t* in, float* Ks, float* Vs, int tid) {
-  const uint4* i4 = reinterpret_cast<const uint4*>(in);
-  for (int ci = tid; ci < 8 * D; ci += 256) {
-    const uint4 q = i4[ci];
-    const uint32_t w[4] = {q.x, q.y, q.z, q.w};
-    if (ci < 4 * D) {
-      const int tau = ci / (2 * D), rem = ci % (2 * D);
-      const int lam = rem & 63, j = rem >> 6;
-      const int t = 16 * tau + (lam & 15), c0 = 32 * j + 8 * (lam >> 4);
-#pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        Ks[t * LD + c0 + 2 * p] = __uint_as_float(w[p] << 16);
-        Ks[t * LD + c0 + 2 * p + 1] = __uint_as_float(w[p] & 0xffff0000u);
-      }
-    } else {
-      const int cv = ci - 4 * D;
-      const int lam = cv & 63, m = cv >> 6;
-      const int c = 16 * m + (lam & 15), kg = lam >> 4;
-#pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        const int s0 = 2 * p, s1 = 2 * p + 1;
-        const int t0 = 16 * (s0 >> 2) + 4 * kg + (s0 & 3), t1 = 16 * (s1 >> 2) + 4 * kg + (s1 & 3);
-        Vs[t0 * LD + c] = __uint_as_float(w[p] << 16);
-        Vs[t1 * LD + c] = __uint_as_float(w[p] & 0xffff0000u);
-      }
-    }
-  }
-}
-
-// min / max over the N consecutive lanes of a group (N = 1, 2, 4), every lane of the
-// group ending with the result.
-template <int N>
-__device__ __forceinline__ float group_min(float x) {
-  if constexpr (N >= 2) x = fminf(x, dpp<kQuadXor1>(x));
-  if constexpr (N >= 4) x = fminf(x, dpp<kQuadXor2>(x));
-  return x;
-}
-template <int N>
-__device__ __forceinline__ float group_max(float x) {
-  if constexpr (N >= 2) x = fmaxf(x, dpp<kQuadXor1>(x));
-  if constexpr (N >= 4) x = fmaxf(x, dpp<kQuadXor2>(x));
+// x, opaque to the compiler: what is derived from it is computed again rather than
+// kept in registers from an earlier phase.
+__device__ __forceinline__ int renewed(int x) {
+  asm("" : "+v"(x));
   return x;
 }
 
-// Quantise the 32 tokens staged in LDS (Ks, Vs: fp32 rows of LD floats) into one
-// block of BITS-bit codes plus metadata at `out`.  Called by all 256 threads.
-template <int D, int BITS, int QS>
-__device__ __forceinline__ void write_quant_block(const float* Ks, const float* Vs, float* kmeta, float* vmeta,
-                                                  uint8_t* out, int tid) {
-  constexpr int LD = D + 4;
-  {
-    constexpr float levels = (float)((1 << BITS) - 1);
+// Token of row n in the lanes of token set tg.
+__device__ __forceinline__ int row_token(int n, int tg) { return 16 * (n >> 2) + 4 * tg + (n & 3); }
 
-    // ---- group metadata ----
-    constexpr int NG64 = D / 64;  // GROUP64 channel groups
-    if constexpr (QS == kQsKivi) {
-      {  // K: channel c over the block's 32 tokens, TPC threads per channel
-        constexpr int TPC = 256 / D, TOK = 32 / TPC;
-        const int c = tid / TPC, t0 = TOK * (tid % TPC);
-        float mn = Ks[t0 * LD + c], mx = mn;
+__device__ __forceinline__ u4v pack_bf16(f4 lo, f4 hi) {
+  u4v r;
 #pragma unroll
-        for (int t = 1; t < TOK; ++t) {
-          const float x = Ks[(t0 + t) * LD + c];
-          mn = fminf(mn, x);
-          mx = fmaxf(mx, x);
-        }
-        mn = group_min<TPC>(mn);
-        mx = group_max<TPC>(mx);
-        if (tid % TPC == 0) {
-          kmeta[c] = (float)(_Float16)((mx - mn) / levels);
-          kmeta[D + c] = (float)(_Float16)mn;
-        }
-      }
-      {  // V: token t, channel group g (32 channels), TPG threads per group
-        constexpr int NG = D / 32, TPG = 256 / (32 * NG), CH = 32 / TPG;
-        const int pr = tid / TPG, t = pr / NG, g = pr % NG;
-        const float* row = &Vs[t * LD + 32 * g + CH * (tid % TPG)];
-        f4 x = *reinterpret_cast<const f4*>(row);
-        float mn = fminf(fminf(x[0], x[1]), fminf(x[2], x[3])), mx = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
+  for (int p = 0; p < 4; ++p) {
+    const float x0 = p < 2 ? lo[2 * p] : hi[2 * p - 4], x1 = p < 2 ? lo[2 * p + 1] : hi[2 * p - 3];
+    r[p] = (uint32_t)f32_to_bf16_bits(x0) | ((uint32_t)f32_to_bf16_bits(x1) << 16);
+  }
+  return r;
+}
+
+// A lane's eight rows of eight channels, as loaded: bf16 packed, or fp32.
+template <bool F32>
+struct Rows;
+template <>
+struct Rows<false> {
+  u4v w[8];
+  __device__ __forceinline__ void load(const void* base, int64_t e, int n) {
+    w[n] = *reinterpret_cast<const u4v*>(static_cast<const uint16_t*>(base) + e);
+  }
+  __device__ __forceinline__ float get(int n, int c) const {
+    const uint32_t x = w[n][c >> 1];
+    return __uint_as_float(c & 1 ? x & 0xffff0000u : x << 16);
+  }
+  __device__ __forceinline__ u4v bf16(int n) const { return w[n]; }
+  // Forget the conversions of an earlier pass over the rows (64 registers if kept).
+  __device__ __forceinline__ void renew() {
 #pragma unroll
-        for (int c = 4; c < CH; c += 4) {
-          x = *reinterpret_cast<const f4*>(row + c);
-          mn = fminf(mn, fminf(fminf(x[0], x[1]), fminf(x[2], x[3])));
-          mx = fmaxf(mx, fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])));
-        }
-        mn = group_min<TPG>(mn);
-        mx = group_max<TPG>(mx);
-        if (tid % TPG == 0) {
-          vmeta[2 * (t * NG + g)] = (float)(_Float16)((mx - mn) / levels);
-          vmeta[2 * (t * NG + g) + 1] = (float)(_Float16)mn;
-        }
-      }
-    } else if constexpr (QS == kQsG64) {  // (token, 64 channels) of K then of V, TPG threads per group
-      constexpr int NGR = 2 * 32 * NG64, TPG = 256 / NGR, CH = 64 / TPG;
-      const int pr = tid / TPG, isv = pr >= 32 * NG64, r = pr % (32 * NG64), t = r / NG64, g = r % NG64;
-      const float* row = (isv ? &Vs[t * LD] : &Ks[t * LD]) + 64 * g + CH * (tid % TPG);
-      f4 x = *reinterpret_cast<const f4*>(row);
-      float mn = fminf(fminf(x[0], x[1]), fminf(x[2], x[3])), mx = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
+    for (int n = 0; n < 8; ++n)
 #pragma unroll
-      for (int c = 4; c < CH; c += 4) {
-        x = *reinterpret_cast<const f4*>(row + c);
-        mn = fminf(mn, fminf(fminf(x[0], x[1]), fminf(x[2], x[3])));
-        mx = fmaxf(mx, fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])));
+      for (int p = 0; p < 4; ++p) {
+        uint32_t x = w[n][p];
+        asm("" : "+v"(x));
+        w[n][p] = x;
       }
-      mn = group_min<TPG>(mn);
-      mx = group_max<TPG>(mx);
-      if (tid % TPG == 0) {
-        float* meta = isv ? vmeta : kmeta;
-        meta[2 * (t * NG64 + g)] = (float)(_Float16)((mx - mn) / levels);
-        meta[2 * (t * NG64 + g) + 1] = (float)(_Float16)mn;
-      }
-    } else {  // SYMROW: one scale per token row of K (rows 0..31) and V (rows 32..63), 4 threads per row
-      constexpr int CH = D / 4;
-      const int r = tid >> 2;
-      const float* row = (r < 32 ? &Ks[r * LD] : &Vs[(r - 32) * LD]) + CH * (tid & 3);
-      float am = 0.0f;
+  }
+};
+template <>
+struct Rows<true> {
+  f4 lo[8], hi[8];
+  __device__ __forceinline__ void load(const void* base, int64_t e, int n) {
+    const f4* p = reinterpret_cast<const f4*>(static_cast<const float*>(base) + e);
+    lo[n] = p[0];
+    hi[n] = p[1];
+  }
+  __device__ __forceinline__ float get(int n, int c) const { return c < 4 ? lo[n][c] : hi[n][c - 4]; }
+  __device__ __forceinline__ u4v bf16(int n) const { return pack_bf16(lo[n], hi[n]); }
+  __device__ __forceinline__ void renew() {}
+};
+
+// min and max of eight values as v_min3 / v_max3 trees.  The instructions are written
+// out: from fminf the compiler first quiets every operand (a v_max of its own per
+// loaded value).  A NaN operand is skipped, as by fminf.
+__device__ __forceinline__ float min3(float a, float b, float c) {
+  float r;
+  asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+__device__ __forceinline__ float max3(float a, float b, float c) {
+  float r;
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+__device__ __forceinline__ float min2(float a, float b) {
+  float r;
+  asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ float max2(float a, float b) {
+  float r;
+  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+template <class F>
+__device__ __forceinline__ float min8(F x) {
+  return min2(min3(min3(x(0), x(1), x(2)), x(3), x(4)), min3(x(5), x(6), x(7)));
+}
+template <class F>
+__device__ __forceinline__ float max8v(F x) {
+  return max2(max3(max3(x(0), x(1), x(2)), x(3), x(4)), max3(x(5), x(6), x(7)));
+}
+// |x| of eight values.
+template <class F>
+__device__ __forceinline__ float amax8(F x) {
+  return max8v([&](int i) { return fabsf(x(i)); });
+}
+
+// ---------------------------------------------------------------------------
+// Quantisers
+// ---------------------------------------------------------------------------
+
+// Scale, reciprocal and zero of one grouped-asymmetric group: s, z the fp16 values
+// (App. C.3) and y = 1/s to an ulp; s = y = 0 stands for the groups whose codes are 0
+// whatever the value (s zero, or beyond fp16: infinite).  (mx - mn) / levels is
+// rounded correctly by one residual step on the product with the constant's
+// reciprocal: the residual is exact (levels has 8 bits), and the quotient's distance
+// from a rounding boundary exceeds the step's error (as in Coder::quotient).
+struct Group {
+  float s, y, z;
+  uint32_t sz;  // the stored pair: scale in the low half, zero in the high half
+};
+template <int BITS>
+__device__ __forceinline__ Group make_group(float mn, float mx) {
+  constexpr float levels = (float)((1 << BITS) - 1), inv = 1.0f / levels;
+  const float d = mx - mn;
+  const float q = fminf(d * inv, 3.402823466e38f);
+  const float sc = __builtin_fmaf(__builtin_fmaf(-levels, q, d), inv, q);
+  const _Float16 s16 = (_Float16)sc, z16 = (_Float16)mn;
+  Group g;
+  const float s = (float)s16;
+  g.z = (float)z16;
+  g.sz = (uint32_t)bitcast<uint16_t>(s16) | ((uint32_t)bitcast<uint16_t>(z16) << 16);
+  const bool live = s > 0.0f && s < __builtin_huge_valf();
+  g.s = live ? s : 0.0f;
+  g.y = live ? __builtin_amdgcn_rcpf(s) : 0.0f;
+  return g;
+}
+
+// 1.5 * 2^23: adding it rounds to the nearest integer (ties to even) into the low bits.
+constexpr float kRound = 12582912.0f;
+
+// The code of x in a grouped-asymmetric group, in the low bits of the result (the bits
+// above hold kRound's).  fp32 (x - z) / s correctly rounded, then rounded to an
+// integer and clamped.  The division: q = a y is within 2 ulp of a / s; r = a - s q is
+// exact in one fma (s has 11 significant bits); q + r y differs from a / s by under
+// 2^-44 relative before its rounding, and a / s lies no closer than 2^-36 to a
+// rounding boundary (a - s m is a whole number of units of a 36-bit product), so the
+// result is the correctly rounded quotient: 4 operations in place of the compiler's
+// 11.  The bound at 512 only matters when a is infinite (z beyond fp16): it keeps the
+// residual infinite instead of NaN.  A NaN (any NaN input) gives code 0.
+template <int BITS>
+__device__ __forceinline__ uint32_t group_code(float x, float s, float y, float z) {
+  constexpr float levels = (float)((1 << BITS) - 1);
+  const float a = x - z;
+  const float q = fminf(a * y, 512.0f);
+  const float t = __builtin_fmaf(__builtin_fmaf(-s, q, a), y, q);
+  return __float_as_uint(__builtin_amdgcn_fmed3f(t, 0.0f, levels) + kRound);
+}
+
+// One symmetric row: the stored bf16 scale; s and y = 1/s of the row scaled by f, a
+// power of two that keeps both away from the denormals; the clamp (0 where the scale
+// is zero).  s = y = 0 for an infinite scale: finite values get code 0.
+struct Row {
+  float s, y, f, hi;
+  uint16_t bits;
+};
+template <int BITS>
+__device__ __forceinline__ Row make_row(float am) {
+  constexpr float q = (float)((1 << (BITS - 1)) - 1);
+  Row r;
+  r.bits = f32_to_bf16_bits(am / q);
+  const float s = bf16_to_f32(r.bits);
+  r.f = s < 0x1p-60f ? 0x1p64f : (s > 0x1p60f ? 0x1p-64f : 1.0f);
+  const bool live = s > 0.0f && s < __builtin_huge_valf();
+  r.s = live ? s * r.f : 0.0f;
+  r.y = live ? __builtin_amdgcn_rcpf(r.s) : 0.0f;
+  r.hi = s != 0.0f ? q : 0.0f;
+  return r;
+}
+// The stored code of x in a symmetric row (as group_code: s has 8 significant bits).
+template <int BITS>
+__device__ __forceinline__ uint32_t row_code(float x, const Row& r) {
+  const float a = x * r.f;
+  const float q = a * r.y;
+  const float t = __builtin_fmaf(__builtin_fmaf(-r.s, q, a), r.y, q);
+  return __float_as_uint(__builtin_amdgcn_fmed3f(t, -r.hi, r.hi) + (kRound + (float)(1 << (BITS - 1))));
+}
+
+// Eight codes (low bits of b) as a chunk, to the chunk's place at byte `at` of a part.
+// b = 2: the chunk's two bytes sit in the word it shares with its neighbour.
+template <int BITS>
+__device__ __forceinline__ void store_chunk(uint8_t* part, int at, const uint32_t (&b)[8]) {
+  if constexpr (BITS == 8) {
+    u2v w;
 #pragma unroll
-      for (int c = 0; c < CH; c += 4) {
-        const f4 x = *reinterpret_cast<const f4*>(row + c);
-        am = fmaxf(am, fmaxf(fmaxf(fabsf(x[0]), fabsf(x[1])), fmaxf(fabsf(x[2]), fabsf(x[3]))));
-      }
-      am = group_max<4>(am);
-      if ((tid & 3) == 0) {
-        constexpr float q = (float)((1 << (BITS - 1)) - 1);
-        const float sc = bf16_to_f32(f32_to_bf16_bits(am / q));
-        if (r < 32) kmeta[r] = sc;
-        else vmeta[r - 32] = sc;
-      }
+    for (int h = 0; h < 2; ++h) {
+      const uint32_t lo = __builtin_amdgcn_perm(b[4 * h + 1], b[4 * h], 0x0c0c0400u);
+      const uint32_t hi = __builtin_amdgcn_perm(b[4 * h + 3], b[4 * h + 2], 0x04000c0cu);
+      w[h] = lo | hi;
     }
-    __syncthreads();
-
-    // ---- codes: whole 32-bit words ----
-    uint32_t* ow = reinterpret_cast<uint32_t*>(out);
-    constexpr int cb = 4 * D * BITS;          // bytes per code region
-    constexpr int lane_bytes_k = D * BITS / 32;
-    constexpr int lane_bytes_v = D * BITS / 16;
-    constexpr int nslot = 32 / BITS;          // codes per word
-    for (int wi = tid; wi < 2 * cb / 4; wi += 256) {
-      const bool isv = wi >= cb / 4;
-      const int wb = 4 * (isv ? wi - cb / 4 : wi);  // byte offset inside the region
-      int lam, r2, tau = 0;  // lane and byte of its share held by this word
-      if (!isv) {
-        tau = wb / (2 * D * BITS);
-        share_of(lane_bytes_k, wb % (2 * D * BITS), lam, r2);
-      } else {
-        share_of(lane_bytes_v, wb, lam, r2);
-      }
-      const int i = lam & 15, kg = lam >> 4;
-      // the chunk x and first slot s0 of the word's codes
-      int x0, s0;
-      if constexpr (BITS == 8) { x0 = r2 / 8; s0 = 4 * ((r2 % 8) / 4); }
-      else if constexpr (BITS == 4) { x0 = r2 / 4; s0 = 0; }
-      else { x0 = r2 / 2; s0 = 0; }
-      uint32_t word = 0;
+    *reinterpret_cast<u2v*>(part + at) = w;
+  } else {
+    // slot s at bit 16 (s%2) + BITS (s/2): the high bits of the shifted terms fall
+    // above bit 22 and are dropped with the upper halves
+    uint32_t lo = b[0], hi = b[1];
 #pragma unroll
-      for (int qq = 0; qq < nslot; ++qq) {
-        int x, sl, bit;
-        if constexpr (BITS == 8) { x = x0; sl = s0 + qq; bit = 8 * qq; }
-        else if constexpr (BITS == 4) { x = x0; sl = qq; bit = 16 * (sl & 1) + 4 * (sl >> 1); }
-        else { x = x0 + (qq >> 3); sl = qq & 7; bit = 16 * (sl & 1) + 2 * (sl >> 1) + 8 * (qq >> 3); }
-        uint32_t u;
-        if (!isv) {
-          const int t = 16 * tau + i, c = 32 * x + 8 * kg + sl;
-          const float xv = Ks[t * LD + c];
-          if constexpr (QS == kQsKivi) {
-            u = kivi_code(xv, kmeta[c], kmeta[D + c], levels);
-          } else if constexpr (QS == kQsG64) {
-            const int gi = 2 * (t * NG64 + (c >> 6));
-            u = kivi_code(xv, kmeta[gi], kmeta[gi + 1], levels);
-          } else {
-            u = sym_code(xv, kmeta[t], BITS);
-          }
-        } else {
-          const int c = 16 * x + i, t = 16 * (sl >> 2) + 4 * kg + (sl & 3);
-          const float xv = Vs[t * LD + c];
-          if constexpr (QS == kQsKivi) {
-            const int g = c >> 5;
-            u = kivi_code(xv, vmeta[2 * (t * (D / 32) + g)], vmeta[2 * (t * (D / 32) + g) + 1], levels);
-          } else if constexpr (QS == kQsG64) {
-            const int gi = 2 * (t * NG64 + (c >> 6));
-            u = kivi_code(xv, vmeta[gi], vmeta[gi + 1], levels);
-          } else {
-            u = sym_code(xv, vmeta[t], BITS);
-          }
-        }
-        word |= u << bit;
-      }
-      ow[wi] = word;
+    for (int p = 1; p < 4; ++p) {
+      lo |= b[2 * p] << (BITS * p);
+      hi |= b[2 * p + 1] << (BITS * p);
     }
-
-    // ---- metadata stores ----
-    uint16_t* om = reinterpret_cast<uint16_t*>(out + 2 * cb);
-    if constexpr (QS == kQsG64) {
-      for (int idx = tid; idx < 2 * D; idx += 256) {
-        float val;
-        if (idx < D) {  // K: ((tau*4 + kg)*NG*2 + g*2 + w)*4 + e, token 16 tau + 4 kg + e
-          const int e = idx & 3, w = (idx >> 2) & 1, g = (idx >> 3) % NG64, tk = (idx >> 3) / NG64;
-          const int t = 16 * (tk >> 2) + 4 * (tk & 3) + e;
-          val = kmeta[2 * (t * NG64 + g) + w];
-        } else {  // V: ((g*2 + w)*4 + kg)*8 + s, token 16 (s/4) + 4 kg + (s%4)
-          const int e = idx - D;
-          const int sl = e & 7, kg = (e >> 3) & 3, w = (e >> 5) & 1, g = e >> 6;
-          const int t = 16 * (sl >> 2) + 4 * kg + (sl & 3);
-          val = vmeta[2 * (t * NG64 + g) + w];
-        }
-        om[idx] = bitcast<uint16_t>((_Float16)val);  // exact: the value is an fp16
-      }
-    } else if constexpr (QS == kQsKivi) {
-      for (int idx = tid; idx < 4 * D; idx += 256) {
-        float val;
-        if (idx < 2 * D) {
-          val = kmeta[idx];  // scale[0..D) then zero[0..D)
-        } else {
-          const int e = idx - 2 * D;  // ((g*2 + w)*4 + kg)*8 + s
-          const int sl = e & 7, kg = (e >> 3) & 3, w = (e >> 5) & 1, g = e >> 6;
-          const int t = 16 * (sl >> 2) + 4 * kg + (sl & 3);
-          val = vmeta[2 * (t * (D / 32) + g) + w];
-        }
-        om[idx] = bitcast<uint16_t>((_Float16)val);  // exact: the value is an fp16
-      }
-    } else if (tid < 64) {
-      om[tid] = f32_to_bf16_bits(tid < 32 ? kmeta[tid] : vmeta[tid - 32]);
+    if constexpr (BITS == 4) {
+      *reinterpret_cast<uint32_t*>(part + at) = __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+    } else {
+      part[at] = (uint8_t)lo;
+      part[at + 2] = (uint8_t)hi;
     }
   }
 }
 
-// One workgroup writes one 32-token block of one stream, with BITS-bit codes (or
-// bf16 at BITS = 16; a stream's tail block is always bf16).
-template <int D, int BITS, int QS>
-__global__ __launch_bounds__(256) void compress_kernel(CompressArgs a) {
-  constexpr int LD = D + 4;  // padded LDS row (floats), rows 16-byte aligned
-  __shared__ float Ks[32 * LD];
-  __shared__ float Vs[32 * LD];
-  __shared__ float kmeta[2 * D];          // KIVI32: scale, zero per channel; GROUP64: per (token, group); SYMROW: row scale
-  __shared__ float vmeta[2 * 32 * (D / 32)];
+// Byte of the K chunk (token t, channels 8q..8q+7) and of the V chunk (channel c, token
+// set tg) in the code parts of a block, by the share layout of kvk.h.
+template <int D, int BITS>
+__device__ __forceinline__ int k_chunk_byte(int t, int q) {
+  const int j = q >> 2, lam = 16 * (q & 3) + (t & 15), tile = 2 * D * BITS * (t >> 4);
+  constexpr int P = D * BITS / 32;
+  if constexpr (BITS == 2) return tile + share_byte(P, lam, 4 * (j >> 1)) + (j & 1);
+  return tile + share_byte(P, lam, BITS * j);
+}
+template <int D, int BITS>
+__device__ __forceinline__ int v_chunk_byte(int c, int tg) {
+  const int m = c >> 4, lam = 16 * tg + (c & 15);
+  constexpr int P = D * BITS / 16;
+  if constexpr (BITS == 2) return 4 * D * BITS + share_byte(P, lam, 4 * (m >> 1)) + (m & 1);
+  return 4 * D * BITS + share_byte(P, lam, BITS * m);
+}
 
-  const int tid = threadIdx.x;
+// Reduction over the token sets of one channel's minimum or maximum, all lanes ending
+// with it (d_h 64: the sets are 8 and 16 lanes apart).
+__device__ __forceinline__ float sets_min64(float x) {
+  x = min2(x, dpp<0x128>(x));  // row_ror:8
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return min2(__uint_as_float(a[0]), __uint_as_float(a[1]));
+}
+__device__ __forceinline__ float sets_max64(float x) {
+  x = max2(x, dpp<0x128>(x));
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return max2(__uint_as_float(a[0]), __uint_as_float(a[1]));
+}
+
+struct Pair {
+  float a, b;
+};
+__device__ __forceinline__ Pair swap16(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return {__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+__device__ __forceinline__ Pair swap32(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return {__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+// x of the four 16-lane rows to every lane: row r's value in out[r].
+__device__ __forceinline__ void gather_rows(float x, float (&out)[4]) {
+  const Pair h = swap32(x, x);  // rows 0, 1 twice; rows 2, 3 twice
+  const Pair l = swap16(h.a, h.a), u = swap16(h.b, h.b);
+  out[0] = l.a;
+  out[1] = l.b;
+  out[2] = u.a;
+  out[3] = u.b;
+}
+
+// KIVI32 key metadata: every lane's eight channel groups, and the stored pairs into
+// kmeta (fp16 scale[D] then zero[D]).
+template <int D, int BITS, class R>
+__device__ __forceinline__ void kivi_key_groups(const R& rows, int q, int tg, uint16_t* kmeta, float (&s)[8],
+                                                float (&y)[8], float (&z)[8]) {
+  float mn[8], mx[8];
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    mn[c] = min8([&](int n) { return rows.get(n, c); });
+    mx[c] = max8v([&](int n) { return rows.get(n, c); });
+  }
+  if constexpr (D == 128) {
+    // the token sets are the four 16-lane rows: each swap finishes half of two
+    // channels' reductions, so that row tg ends with the channels
+    // k + 2 (tg / 2) + 4 (tg % 2), k = 0, 1, forms their groups, and the rows share them
+    float rn[4], rx[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const Pair a = swap16(mn[k], mn[k + 4]), b = swap16(mx[k], mx[k + 4]);
+      rn[k] = min2(a.a, a.b);
+      rx[k] = max2(b.a, b.b);
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const Pair a = swap32(rn[k], rn[k + 2]), b = swap32(rx[k], rx[k + 2]);
+      const Group g = make_group<BITS>(min2(a.a, a.b), max2(b.a, b.b));
+      const int c = 8 * q + k + 2 * (tg >> 1) + 4 * (tg & 1);
+      kmeta[c] = (uint16_t)g.sz;
+      kmeta[D + c] = (uint16_t)(g.sz >> 16);
+      float t[4];
+      constexpr int kOf[4] = {0, 4, 2, 6};
+      gather_rows(g.s, t);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) s[k + kOf[r]] = t[r];
+      gather_rows(g.y, t);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) y[k + kOf[r]] = t[r];
+      gather_rows(g.z, t);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) z[k + kOf[r]] = t[r];
+    }
+  } else {
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const Group g = make_group<BITS>(sets_min64(mn[c]), sets_max64(mx[c]));
+      if (tg == 0) {
+        kmeta[8 * q + c] = (uint16_t)g.sz;
+        kmeta[D + 8 * q + c] = (uint16_t)(g.sz >> 16);
+      }
+      s[c] = g.s;
+      y[c] = g.y;
+      z[c] = g.z;
+    }
+  }
+}
+
+// Per-token groups of N lanes (32 channels: 4; 64: 8), every lane's eight tokens: the
+// stored pairs in sz.
+template <int BITS, int N, class R>
+__device__ __forceinline__ void token_groups(const R& rows, int q, float (&s)[8], float (&y)[8], float (&z)[8],
+                                             uint32_t (&sz)[8]) {
+  float mn[8], mx[8];
+#pragma unroll
+  for (int n = 0; n < 8; ++n) {
+    mn[n] = min8([&](int c) { return rows.get(n, c); });
+    mx[n] = max8v([&](int c) { return rows.get(n, c); });
+  }
+  if constexpr (N == 4) {
+    // a quad's lane finishes two of the eight tokens (2 k + q%2 + (q/2)%2 * 4) and the
+    // others take the results from it
+    const bool o1 = q & 1, o2 = q & 2;
+    float an[4], ax[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      an[k] = min2(o1 ? mn[2 * k + 1] : mn[2 * k], dpp<kQuadXor1>(o1 ? mn[2 * k] : mn[2 * k + 1]));
+      ax[k] = max2(o1 ? mx[2 * k + 1] : mx[2 * k], dpp<kQuadXor1>(o1 ? mx[2 * k] : mx[2 * k + 1]));
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const float bn = min2(o2 ? an[k + 2] : an[k], dpp<kQuadXor2>(o2 ? an[k] : an[k + 2]));
+      const float bx = max2(o2 ? ax[k + 2] : ax[k], dpp<kQuadXor2>(o2 ? ax[k] : ax[k + 2]));
+      const Group g = make_group<BITS>(bn, bx);
+      const float szf = __uint_as_float(g.sz);
+#define KVK_FROM_QUAD(E, CTRL) \
+  { \
+    constexpr int n = (E & 1) + 2 * (E >> 1) * 2; \
+    s[2 * k + n] = dpp<CTRL>(g.s); \
+    y[2 * k + n] = dpp<CTRL>(g.y); \
+    z[2 * k + n] = dpp<CTRL>(g.z); \
+    sz[2 * k + n] = __float_as_uint(dpp<CTRL>(szf)); \
+  }
+      KVK_FROM_QUAD(0, 0x00) KVK_FROM_QUAD(1, 0x55) KVK_FROM_QUAD(2, 0xAA) KVK_FROM_QUAD(3, 0xFF)
+#undef KVK_FROM_QUAD
+    }
+  } else {
+#pragma unroll
+    for (int n = 0; n < 8; ++n) {
+      float a = mn[n], b = mx[n];
+      a = min2(a, dpp<kQuadXor1>(a));
+      b = max2(b, dpp<kQuadXor1>(b));
+      a = min2(a, dpp<kQuadXor2>(a));
+      b = max2(b, dpp<kQuadXor2>(b));
+      a = min2(a, dpp<kHalfRowMirror>(a));
+      b = max2(b, dpp<kHalfRowMirror>(b));
+      const Group g = make_group<BITS>(a, b);
+      s[n] = g.s;
+      y[n] = g.y;
+      z[n] = g.z;
+      sz[n] = g.sz;
+    }
+  }
+}
+
+__device__ __forceinline__ u4v low_halves(const uint32_t (&x)[8]) {
+  u4v r;
+#pragma unroll
+  for (int p = 0; p < 4; ++p) r[p] = __builtin_amdgcn_perm(x[2 * p + 1], x[2 * p], 0x05040100u);
+  return r;
+}
+__device__ __forceinline__ u4v high_halves(const uint32_t (&x)[8]) {
+  u4v r;
+#pragma unroll
+  for (int p = 0; p < 4; ++p) r[p] = __builtin_amdgcn_perm(x[2 * p + 1], x[2 * p], 0x07060302u);
+  return r;
+}
+
+// Keys (codes and metadata) of a block into its LDS image.
+template <int D, int BITS, int QS, class R>
+__device__ __forceinline__ void quant_keys(R& rows, int q, int tg, uint8_t* img) {
+  tg = renewed(tg);
+  uint8_t* meta = img + 8 * D * BITS;
+  float s[8], y[8], z[8];
+  if constexpr (QS == kQsKivi) {
+    kivi_key_groups<D, BITS>(rows, q, tg, reinterpret_cast<uint16_t*>(meta), s, y, z);
+  } else if constexpr (QS == kQsG64) {
+    uint32_t sz[8];
+    token_groups<BITS, 8>(rows, q, s, y, z, sz);
+    if (q % 8 == 0) {  // fp16 index ((tau*4 + kg)*NG*2 + g*2 + w)*4 + e
+      const u4v sc = low_halves(sz), ze = high_halves(sz);
+#pragma unroll
+      for (int tau = 0; tau < 2; ++tau) {
+        u4v* m4 = reinterpret_cast<u4v*>(meta + 16 * ((tau * 4 + tg) * (D / 64) + q / 8));
+        *m4 = u4v{sc[2 * tau], sc[2 * tau + 1], ze[2 * tau], ze[2 * tau + 1]};
+      }
+    }
+  }
+  rows.renew();
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int n = 0; n < 8; ++n) {
+    uint32_t b[8];
+    const int t = row_token(n, tg);
+    if constexpr (QS == kQsSym) {
+      float am = amax8([&](int c) { return rows.get(n, c); });
+      am = D == 128 ? max16(am) : max8(am);
+      const Row r = make_row<BITS>(am);
+      if (q == 0) reinterpret_cast<uint16_t*>(meta)[t] = r.bits;
+#pragma unroll
+      for (int c = 0; c < 8; ++c) b[c] = row_code<BITS>(rows.get(n, c), r);
+    } else {
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        const int g = QS == kQsKivi ? c : n;
+        b[c] = group_code<BITS>(rows.get(n, c), s[g], y[g], z[g]);
+      }
+    }
+    store_chunk<BITS>(img, k_chunk_byte<D, BITS>(t, q), b);
+    __builtin_amdgcn_sched_barrier(0);  // chunk after chunk: interleaved ones spill
+  }
+}
+
+// Values of a block into its LDS image.
+template <int D, int BITS, int QS, class R>
+__device__ __forceinline__ void quant_values(R& rows, int q, int tg, uint8_t* img) {
+  tg = renewed(tg);
+  uint8_t* meta = img + 8 * D * BITS;
+  if constexpr (QS == kQsSym) {
+    Row r[8];
+#pragma unroll
+    for (int n = 0; n < 8; ++n) {
+      float am = amax8([&](int c) { return rows.get(n, c); });
+      am = D == 128 ? max16(am) : max8(am);
+      r[n] = make_row<BITS>(am);
+      if (q == 0) reinterpret_cast<uint16_t*>(meta)[32 + row_token(n, tg)] = r[n].bits;
+    }
+    rows.renew();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      uint32_t b[8];
+#pragma unroll
+      for (int n = 0; n < 8; ++n) b[n] = row_code<BITS>(rows.get(n, c), r[n]);
+      store_chunk<BITS>(img, v_chunk_byte<D, BITS>(8 * q + c, tg), b);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  } else {
+    constexpr int GL = QS == kQsKivi ? 4 : 8;  // lanes of a group
+    float s[8], y[8], z[8];
+    uint32_t sz[8];
+    token_groups<BITS, GL>(rows, q, s, y, z, sz);
+    if (q % GL == 0) {  // fp16 index ((g*2 + w)*4 + kg)*8 + s
+      u4v* m4 = reinterpret_cast<u4v*>(meta + (QS == kQsKivi ? 4 * D : 2 * D)) + 8 * (q / GL) + tg;
+      m4[0] = low_halves(sz);
+      m4[4] = high_halves(sz);
+    }
+    rows.renew();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      uint32_t b[8];
+#pragma unroll
+      for (int n = 0; n < 8; ++n) b[n] = group_code<BITS>(rows.get(n, c), s[n], y[n], z[n]);
+      store_chunk<BITS>(img, v_chunk_byte<D, BITS>(8 * q + c, tg), b);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+}
+
+// bf16 K part (64 D bytes) of a block into LDS: a lane's row is a 16-byte piece.
+template <int D, class R>
+__device__ __forceinline__ void bf16_keys(const R& rows, int q, int tg, uint8_t* img) {
+#pragma unroll
+  for (int n = 0; n < 8; ++n) {
+    const int t = row_token(n, tg);
+    *reinterpret_cast<u4v*>(img + 32 * D * (t >> 4) + 1024 * (q >> 2) + 16 * (16 * (q & 3) + (t & 15))) = rows.bf16(n);
+  }
+}
+// bf16 V part (64 D bytes): a channel's eight tokens are a 16-byte piece.
+template <int D, class R>
+__device__ __forceinline__ void bf16_values(const R& rows, int q, int tg, uint8_t* img) {
+  u4v w[8];
+#pragma unroll
+  for (int n = 0; n < 8; ++n) w[n] = rows.bf16(n);
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    u4v o;
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+      o[p] = __builtin_amdgcn_perm(w[2 * p + 1][c >> 1], w[2 * p][c >> 1], c & 1 ? 0x07060302u : 0x05040100u);
+    const int ch = 8 * q + c;
+    *reinterpret_cast<u4v*>(img + 1024 * (ch >> 4) + 16 * (16 * tg + (ch & 15))) = o;
+  }
+}
+
+// Order a wave's LDS accesses (one wave's run in order; this keeps the compiler's
+// order and waits for the writes).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// The first `bytes` of an LDS image to global memory, by the lanes of the block.
+template <int D>
+__device__ __forceinline__ void copy_out(const uint8_t* img, uint8_t* out, int bytes, int l) {
+  wave_lds_fence();
+  for (int o = 16 * l; o < bytes; o += 16 * Lanes<D>::kPerBlock)
+    *reinterpret_cast<u4v*>(out + o) = *reinterpret_cast<const u4v*>(img + o);
+  wave_lds_fence();
+}
+
+// Bytes of a quantised block, and of the LDS image of a block.
+template <int D, int BITS, int QS>
+constexpr int quant_bytes() {
+  return QS == kQsKivi ? 8 * D * (BITS + 1) : QS == kQsSym ? 8 * D * BITS + 128 : 8 * D * BITS + 4 * D;
+}
+template <int D, int BITS, int QS>
+constexpr int image_bytes() {
+  return BITS == 16 || quant_bytes<D, BITS, QS>() < 64 * D ? 64 * D : quant_bytes<D, BITS, QS>();
+}
+
+// The input elements of a lane's rows: stored tokens tok0 .. (none past `last`), through
+// the keep list under eviction.
+template <int D>
+__device__ __forceinline__ void row_elements(const CompressArgs& a, int in_stream, int tok0, int last, int q, int tg,
+                                             int64_t (&e)[8]) {
+  int pos[8];
+#pragma unroll
+  for (int n = 0; n < 8; ++n) {
+    pos[n] = tok0 + row_token(n, tg);
+    pos[n] = pos[n] < last ? pos[n] : last;
+  }
+  if (a.keep) {
+    const int32_t* keep = a.keep + (int64_t)in_stream * a.n_stored;
+#pragma unroll
+    for (int n = 0; n < 8; ++n) pos[n] = keep[pos[n]];
+#pragma unroll
+    for (int n = 0; n < 8; ++n) pos[n] = pos[n] < 0 ? 0 : (pos[n] >= a.n_tokens ? a.n_tokens - 1 : pos[n]);
+  }
+#pragma unroll
+  for (int n = 0; n < 8; ++n) e[n] = ((int64_t)in_stream * a.n_tokens + pos[n]) * D + 8 * q;
+}
+
+// One wave writes one 32-token block of one stream (two at d_h 64), with BITS-bit codes
+// (or bf16 at BITS = 16; a stream's tail block is always bf16).  The keys' and values'
+// loads are all issued first for bf16 inputs (16 KiB in flight per wave).
+//
+// Bound: HBM and the vector units about equally (d_h 128, KIVI32: about 14 vector
+// operations per value; the input is read and the codes are written once).
+template <int D, int BITS, int QS, bool F32>
+__global__ __launch_bounds__(256, F32 ? 3 : 4) void compress_kernel(CompressArgs a) {
+  using L = Lanes<D>;
+  constexpr int kImg = image_bytes<D, BITS, QS>();
+  __shared__ __align__(16) uint8_t img_all[4 * L::kBlocks * kImg];
+
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l = lane % L::kPerBlock, q = l % L::kQ, tg = l / L::kQ, sub = lane / L::kPerBlock;
   const int nblk = a.nbf + 1;
-  const int stream = blockIdx.x / nblk;  // of the launch
-  const int blk = blockIdx.x % nblk;
+  const uint32_t id = (blockIdx.x * 4 + wave) * L::kBlocks + sub;
+  if (id >= (uint32_t)a.n_streams * nblk) return;
+  const int stream = id / (uint32_t)nblk;  // of the launch
+  const int blk = id - (uint32_t)stream * nblk;
   const bool tail = blk == a.nbf;
   const int tok0 = blk * 32;
-  const int ntok = tail ? a.n_stored - tok0 : 32;  // valid tokens of this block
-  int in_stream = stream;                          // of the inputs
+  int in_stream = stream;               // of the inputs
   uint8_t* sbase = a.region + (int64_t)stream * a.stream_bytes;
   if (a.n_seq > 0) {
     const int j = stream / a.Hkv, h = stream - j * a.Hkv;
@@ -391,15 +651,52 @@ __global__ __launch_bounds__(256) void compress_kernel(CompressArgs a) {
     sbase = a.region + a.seq_region[j] + (int64_t)h * a.stream_bytes;
   }
 
-  stage_block<D, LD>(a, in_stream, tok0, ntok, Ks, Vs, tid);
-  __syncthreads();
-
+  uint8_t* img = img_all + (wave * L::kBlocks + sub) * kImg;
   uint8_t* out = sbase + (tail ? (int64_t)a.nb_cap * a.block_bytes : (int64_t)blk * a.block_bytes);
+  Rows<F32> k, v;
+  int64_t e[8];
   if (BITS == 16 || tail) {
-    write_bf16_block<D, LD>(Ks, Vs, out, tid);
+    row_elements<D>(a, in_stream, tok0, tail ? a.n_stored - 1 : tok0 + 31, q, tg, e);
+#pragma unroll
+    for (int n = 0; n < 8; ++n) k.load(a.k, e[n], n);
+    if constexpr (!F32) {
+#pragma unroll
+      for (int n = 0; n < 8; ++n) v.load(a.v, e[n], n);
+    }
+    const int ntok = tail ? a.n_stored - tok0 : 32;  // valid tokens of this block; zeros after them
+    Rows<false> r;
+#pragma unroll
+    for (int n = 0; n < 8; ++n) r.w[n] = row_token(n, tg) < ntok ? k.bf16(n) : u4v{0, 0, 0, 0};
+    bf16_keys<D>(r, q, tg, img);
+    copy_out<D>(img, out, 64 * D, l);
+    if constexpr (F32) {
+#pragma unroll
+      for (int n = 0; n < 8; ++n) v.load(a.v, e[n], n);
+    }
+#pragma unroll
+    for (int n = 0; n < 8; ++n) r.w[n] = row_token(n, tg) < ntok ? v.bf16(n) : u4v{0, 0, 0, 0};
+    bf16_values<D>(r, q, tg, img);
+    copy_out<D>(img, out + 64 * D, 64 * D, l);
     return;
   }
-  if constexpr (BITS != 16) write_quant_block<D, BITS, QS>(Ks, Vs, kmeta, vmeta, out, tid);
+  if constexpr (BITS != 16) {
+    row_elements<D>(a, in_stream, tok0, tok0 + 31, q, tg, e);
+#pragma unroll
+    for (int n = 0; n < 8; ++n) k.load(a.k, e[n], n);
+    if constexpr (!F32) {
+#pragma unroll
+      for (int n = 0; n < 8; ++n) v.load(a.v, e[n], n);
+    }
+    quant_keys<D, BITS, QS>(k, q, tg, img);
+    if constexpr (F32) {  // not before: the keys' registers are needed
+      __builtin_amdgcn_sched_barrier(0);
+      row_elements<D>(a, in_stream, tok0, tok0 + 31, q, renewed(tg), e);
+#pragma unroll
+      for (int n = 0; n < 8; ++n) v.load(a.v, e[n], n);
+    }
+    quant_values<D, BITS, QS>(v, q, tg, img);
+    copy_out<D>(img, out, quant_bytes<D, BITS, QS>(), l);
+  }
 }
 
 // Decode-time append of one token to every anchor of a layer range.
@@ -447,36 +744,67 @@ __global__ __launch_bounds__(256) void tail_write_kernel(AppendArgs a) {
   *reinterpret_cast<uint16_t*>(tailb + v_bf16_byte(D, t, c)) = new_token_bf16(a.v, e, a.in_f32);
 }
 
-// The token that fills the tail (pos % 32 == 31) completes a 32-token group: one
-// workgroup per (stream, anchor) quantises the tail's bf16 values plus the new
-// token (rounded to bf16) into full block pos / 32, exactly as the prefill write
-// quantises a block.  The tail is then empty (its stale slots are never read).
+// The token that fills the tail (pos % 32 == 31) completes a 32-token group: one wave
+// (half a wave at d_h 64) per (stream, anchor) quantises the tail's bf16 values plus
+// the new token (rounded to bf16) into full block pos / 32, exactly as the prefill
+// write quantises a block.  The tail is then empty (its stale slots are never read).
 template <int D, int QS>
 __global__ __launch_bounds__(256) void group_write_kernel(AppendArgs a) {
-  constexpr int LD = D + 4;
-  __shared__ float Ks[32 * LD];
-  __shared__ float Vs[32 * LD];
-  __shared__ float kmeta[2 * D];
-  __shared__ float vmeta[2 * 32 * (D / 32)];
-  const int tid = threadIdx.x, sidx = blockIdx.x;
+  using L = Lanes<D>;
+  constexpr int kImg = image_bytes<D, 8, QS>();
+  __shared__ __align__(16) uint8_t img_all[4 * L::kBlocks * kImg];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l = lane % L::kPerBlock, q = l % L::kQ, tg = l / L::kQ, sub = lane / L::kPerBlock;
+  const int sidx = (blockIdx.x * 4 + wave) * L::kBlocks + sub;
+  if (sidx >= a.n_streams) return;
   const AppendItem& it = a.items[blockIdx.y];
   uint8_t* base = a.arena + it.region + (int64_t)sidx * it.stream_bytes;
-  uint8_t* tailb = base + (int64_t)a.nb_cap * it.block_bytes;
-  const int64_t e0 = (int64_t)it.row * a.row_stride + (int64_t)(it.s0 + sidx) * D;
-  stage_bf16_block<D, LD>(tailb, Ks, Vs, tid);  // row 31 holds a stale slot until replaced
-  __syncthreads();
-  for (int c = tid; c < D; c += 256) {
-    Ks[31 * LD + c] = bf16_to_f32(new_token_bf16(a.k, e0 + c, a.in_f32));
-    Vs[31 * LD + c] = bf16_to_f32(new_token_bf16(a.v, e0 + c, a.in_f32));
+  const uint8_t* tailb = base + (int64_t)a.nb_cap * it.block_bytes;
+  const int64_t e0 = (int64_t)it.row * a.row_stride + (int64_t)(it.s0 + sidx) * D + 8 * q;
+  // the tail block's pieces are the lane's rows (K) and its channels' tokens (V)
+  Rows<false> k, v;
+  u4v vc[8];
+#pragma unroll
+  for (int n = 0; n < 8; ++n) {
+    k.w[n] = *reinterpret_cast<const u4v*>(tailb + k_bf16_byte(D, row_token(n, tg), 8 * q));
+    vc[n] = *reinterpret_cast<const u4v*>(tailb + 64 * D + share_byte(D, 16 * tg + ((8 * q + n) & 15), q >> 1 << 4));
   }
-  __syncthreads();
+#pragma unroll
+  for (int n = 0; n < 8; ++n)
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+      v.w[n][p] = __builtin_amdgcn_perm(vc[2 * p + 1][n >> 1], vc[2 * p][n >> 1], n & 1 ? 0x07060302u : 0x05040100u);
+  if (tg == 3) {  // row 7 is token 31: the new one in place of a stale slot
+    if (a.in_f32) {
+      Rows<true> x;
+      x.load(a.k, e0, 0);
+      x.load(a.v, e0, 1);
+      k.w[7] = x.bf16(0);
+      v.w[7] = x.bf16(1);
+    } else {
+      k.load(a.k, e0, 7);
+      v.load(a.v, e0, 7);
+    }
+  }
+  uint8_t* img = img_all + (wave * L::kBlocks + sub) * kImg;
   uint8_t* out = base + (int64_t)(a.pos >> 5) * it.block_bytes;
-  switch (it.bits) {
-    case 16: write_bf16_block<D, LD>(Ks, Vs, out, tid); break;
-    case 8: write_quant_block<D, 8, QS>(Ks, Vs, kmeta, vmeta, out, tid); break;
-    case 4: write_quant_block<D, 4, QS>(Ks, Vs, kmeta, vmeta, out, tid); break;
-    default: write_quant_block<D, 2, QS>(Ks, Vs, kmeta, vmeta, out, tid); break;
+  if (it.bits == 16) {
+    bf16_keys<D>(k, q, tg, img);
+    copy_out<D>(img, out, 64 * D, l);
+    bf16_values<D>(v, q, tg, img);
+    copy_out<D>(img, out + 64 * D, 64 * D, l);
+    return;
   }
+#define KVK_GROUP_BITS(B) \
+  { \
+    quant_keys<D, B, QS>(k, q, tg, img); \
+    quant_values<D, B, QS>(v, q, tg, img); \
+    copy_out<D>(img, out, quant_bytes<D, B, QS>(), l); \
+  }
+  if (it.bits == 8) KVK_GROUP_BITS(8)
+  else if (it.bits == 4) KVK_GROUP_BITS(4)
+  else KVK_GROUP_BITS(2)
+#undef KVK_GROUP_BITS
 }
 
 // Test-only dequantiser: one thread per (stream, token, channel).
@@ -534,23 +862,33 @@ __global__ __launch_bounds__(256) void dequant_kernel(const uint8_t* region, int
 using namespace kvk;
 
 // One W1 launch over `nstreams` streams of the arguments' layout.
-static kvk_status launch_w1(const CompressArgs& a, int64_t nstreams, hipStream_t stream) {
-  const int64_t grid = nstreams * (a.nbf + 1);
-  if (grid > 0x7fffffffLL) return fail(KVK_ERR_UNSUPPORTED, "grid too large");
-  const dim3 g3((unsigned)grid), b3(256);
-#define KVK_W1(DD, BB, KK) \
-  if (a.D == DD && a.bits == BB && (BB == 16 || a.qs == KK)) { \
-    hipLaunchKernelGGL((compress_kernel<DD, BB, KK>), g3, b3, 0, stream, a); \
-    launched = true; \
+template <int D, int BITS, int QS>
+static void launch_w1_kernel(const CompressArgs& a, hipStream_t stream) {
+  constexpr int per_wg = 4 * Lanes<D>::kBlocks;
+  const dim3 g((unsigned)(((int64_t)a.n_streams * (a.nbf + 1) + per_wg - 1) / per_wg)), b(256);
+  if (a.in_f32) hipLaunchKernelGGL((compress_kernel<D, BITS, QS, true>), g, b, 0, stream, a);
+  else hipLaunchKernelGGL((compress_kernel<D, BITS, QS, false>), g, b, 0, stream, a);
+}
+template <int D, int QS>
+static bool launch_w1_bits(const CompressArgs& a, hipStream_t stream) {
+  switch (a.bits) {
+    case 16: launch_w1_kernel<D, 16, 0>(a, stream); return true;
+    case 8: launch_w1_kernel<D, 8, QS>(a, stream); return true;
+    case 4: launch_w1_kernel<D, 4, QS>(a, stream); return true;
+    case 2: launch_w1_kernel<D, 2, QS>(a, stream); return true;
   }
-  bool launched = false;
-  KVK_W1(128, 16, 0) else KVK_W1(128, 8, 0) else KVK_W1(128, 4, 0) else KVK_W1(128, 2, 0)
-  else KVK_W1(128, 8, 1) else KVK_W1(128, 4, 1) else KVK_W1(128, 2, 1)
-  else KVK_W1(128, 8, 2) else KVK_W1(128, 4, 2) else KVK_W1(128, 2, 2)
-  else KVK_W1(64, 16, 0) else KVK_W1(64, 8, 0) else KVK_W1(64, 4, 0) else KVK_W1(64, 2, 0)
-  else KVK_W1(64, 8, 1) else KVK_W1(64, 4, 1) else KVK_W1(64, 2, 1)
-  else KVK_W1(64, 8, 2) else KVK_W1(64, 4, 2) else KVK_W1(64, 2, 2)
-#undef KVK_W1
+  return false;
+}
+template <int D>
+static bool launch_w1_scheme(const CompressArgs& a, hipStream_t stream) {
+  return a.qs == KVK_Q_KIVI32 ? launch_w1_bits<D, kQsKivi>(a, stream)
+                              : (a.qs == KVK_Q_SYMROW ? launch_w1_bits<D, kQsSym>(a, stream)
+                                                      : launch_w1_bits<D, kQsG64>(a, stream));
+}
+static kvk_status launch_w1(CompressArgs& a, int64_t nstreams, hipStream_t stream) {
+  if (nstreams * (a.nbf + 1) > 0x7fffffffLL) return fail(KVK_ERR_UNSUPPORTED, "grid too large");
+  a.n_streams = (int32_t)nstreams;
+  const bool launched = a.D == 128 ? launch_w1_scheme<128>(a, stream) : a.D == 64 && launch_w1_scheme<64>(a, stream);
   if (!launched) return fail(KVK_ERR_UNSUPPORTED, "no write kernel for d_h %d, %d bits", a.D, a.bits);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(KVK_ERR_DEVICE, "compress launch: %s", hipGetErrorString(e));
@@ -746,7 +1084,8 @@ static kvk_status append_gqa(const kvk_table* t, int32_t l0, int32_t l1, const v
       if (d.head_dim == 128) hipLaunchKernelGGL(tail_write_kernel<128>, g3, b3, 0, stream, a);
       else hipLaunchKernelGGL(tail_write_kernel<64>, g3, b3, 0, stream, a);
     } else {
-      const dim3 g3((unsigned)a.n_streams, (unsigned)n);
+      const int per_wg = d.head_dim == 128 ? 4 : 8;  // streams of a workgroup
+      const dim3 g3((unsigned)((a.n_streams + per_wg - 1) / per_wg), (unsigned)n);
       if (d.head_dim == 128) {
         if (qs == KVK_Q_KIVI32) hipLaunchKernelGGL((group_write_kernel<128, kQsKivi>), g3, b3, 0, stream, a);
         else if (qs == KVK_Q_GROUP64) hipLaunchKernelGGL((group_write_kernel<128, kQsG64>), g3, b3, 0, stream, a);
