@@ -98,7 +98,7 @@ template <>
 struct Rows<false> {
   u4v w[8];
   __device__ __forceinline__ void load(const void* base, int64_t e, int n) {
-    w[n] = *reinterpret_cast<const u4v*>(static_cast<const uint16_t*>(base) + e);
+    w[n] = __builtin_nontemporal_load(reinterpret_cast<const u4v*>(static_cast<const uint16_t*>(base) + e));
   }
   __device__ __forceinline__ float get(int n, int c) const {
     const uint32_t x = w[n][c >> 1];
@@ -122,8 +122,8 @@ struct Rows<true> {
   f4 lo[8], hi[8];
   __device__ __forceinline__ void load(const void* base, int64_t e, int n) {
     const f4* p = reinterpret_cast<const f4*>(static_cast<const float*>(base) + e);
-    lo[n] = p[0];
-    hi[n] = p[1];
+    lo[n] = __builtin_nontemporal_load(p);
+    hi[n] = __builtin_nontemporal_load(p + 1);
   }
   __device__ __forceinline__ float get(int n, int c) const { return c < 4 ? lo[n][c] : hi[n][c - 4]; }
   __device__ __forceinline__ u4v bf16(int n) const { return pack_bf16(lo[n], hi[n]); }
@@ -586,7 +586,7 @@ template <int D>
 __device__ __forceinline__ void copy_out(const uint8_t* img, uint8_t* out, int bytes, int l) {
   wave_lds_fence();
   for (int o = 16 * l; o < bytes; o += 16 * Lanes<D>::kPerBlock)
-    *reinterpret_cast<u4v*>(out + o) = *reinterpret_cast<const u4v*>(img + o);
+    __builtin_nontemporal_store(*reinterpret_cast<const u4v*>(img + o), reinterpret_cast<u4v*>(out + o));
   wave_lds_fence();
 }
 
