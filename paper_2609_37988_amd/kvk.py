@@ -133,13 +133,16 @@ def _ptr(t: Optional[torch.Tensor]):
     if t is None:
         return None
     _need(t.is_cuda, "buffers must be GPU tensors (got a tensor on the host)")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
-def _stream(stream) -> ctypes.c_void_p:
+def _stream(stream) -> int:
+    """The stream's handle; without one the current stream's of the current device.  The
+    handle is asked for directly: building torch's stream object took 3.0 us of a 15 us
+    decode call."""
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 @dataclass
@@ -169,10 +172,19 @@ class Table:
         self.plan = list(plan)
         self.mla_weights = None  # (w_uk, w_uv) attached by set_mla_weights
         self.plans = None        # per-sequence plans (layer_table_batched)
+        self._arena_bytes = None
 
     @property
     def handle(self):
         return self._h
+
+    @property
+    def arena_bytes(self) -> int:
+        """arena_bytes of table_query, asked once (a table does not change): the whole
+        query with its per-layer lists took 2-6 us of every call that checks an arena."""
+        if self._arena_bytes is None:
+            self._arena_bytes = table_query(self).arena_bytes
+        return self._arena_bytes
 
     def __del__(self):
         if getattr(self, "_h", None) and _lib is not None:
@@ -340,7 +352,7 @@ def compress_layer(t: Table, layer: int, k: torch.Tensor, v: torch.Tensor, n_tok
         _need(keep_idx.dtype == torch.int32 and keep_idx.is_contiguous(),
               "keep_idx must be a contiguous int32 tensor")
         _need(keep_idx.numel() == streams * d.keep_tokens, "keep_idx size must be streams*keep_tokens")
-    _need(_nbytes(arena) >= table_query(t).arena_bytes, "arena smaller than arena_bytes")
+    _need(_nbytes(arena) >= t.arena_bytes, "arena smaller than arena_bytes")
     _check(load().kvk_compress_layer(t.handle, layer, _ptr(k), _ptr(v), _dtype_code(k), n_tokens,
                                      _ptr(keep_idx), _ptr(arena), _stream(stream)))
 
@@ -364,7 +376,7 @@ def compress_layer_project(t: Table, layer: int, x: torch.Tensor, w_dkv: torch.T
               keep_idx.numel() == d.batch * d.keep_tokens, "keep_idx must be int32 [B, keep_tokens]")
     if latent_out is not None:
         _need(latent_out.dtype == torch.bfloat16 and latent_out.is_contiguous(), "latent_out must be contiguous bf16")
-    _need(_nbytes(arena) >= table_query(t).arena_bytes, "arena smaller than arena_bytes")
+    _need(_nbytes(arena) >= t.arena_bytes, "arena smaller than arena_bytes")
     _check(load().kvk_compress_layer_project(t.handle, layer, _ptr(x), _ptr(w_dkv), x.shape[2], _ptr(k_rope),
                                              n_tokens, _ptr(keep_idx), _ptr(arena), _ptr(latent_out),
                                              _stream(stream)))
@@ -386,7 +398,7 @@ def append_token(t: Table, layer_begin: int, layer_end: int, k: torch.Tensor, v:
     else:
         _need(k.numel() == v.numel() == nl * d.batch * d.n_kv_heads * d.head_dim,
               "k/v size must be layers*B*Hkv*d_h")
-    _need(_nbytes(arena) >= table_query(t).arena_bytes, "arena smaller than arena_bytes")
+    _need(_nbytes(arena) >= t.arena_bytes, "arena smaller than arena_bytes")
     _check(load().kvk_append_token(t.handle, layer_begin, layer_end, _ptr(k), _ptr(v), _dtype_code(k),
                                    n_stored, _ptr(arena), _stream(stream)))
 
@@ -504,7 +516,7 @@ def decode_attention(t: Table, layer_begin: int, layer_end: int, q: torch.Tensor
     _need(q.numel() == nl * d.batch * d.n_q_heads * _q_width(d), "q size must be layers*B*Hq*width")
     _need(out.numel() == nl * d.batch * d.n_q_heads * _out_width(d), "out size must be layers*B*Hq*width")
     _check_weights(t, nl, w_uk, w_uv)
-    _need(_nbytes(arena) >= table_query(t).arena_bytes, "arena smaller than arena_bytes")
+    _need(_nbytes(arena) >= t.arena_bytes, "arena smaller than arena_bytes")
     _check(load().kvk_decode_attention(
         t.handle, layer_begin, layer_end, _ptr(q), _dtype_code(q), n_stored, float(scale),
         _ptr(w_uk), _ptr(w_uv), _ptr(arena), _ptr(out), _ptr(workspace),
@@ -534,7 +546,7 @@ def decode_attention_noalloc(t: Table, layer_begin: int, layer_end: int, q: torc
     _need(q.numel() == nl * d.batch * d.n_q_heads * _q_width(d), "q size must be layers*B*Hq*width")
     _need(out.numel() == nl * d.batch * d.n_q_heads * _out_width(d), "out size must be layers*B*Hq*width")
     _check_weights(t, nl, w_uk, w_uv)
-    _need(_nbytes(arena) >= table_query(t).arena_bytes, "arena smaller than arena_bytes")
+    _need(_nbytes(arena) >= t.arena_bytes, "arena smaller than arena_bytes")
     _check(load().kvk_decode_attention_noalloc(
         t.handle, layer_begin, layer_end, _ptr(q), _dtype_code(q), n_stored, float(scale),
         _ptr(w_uk), _ptr(w_uv), _ptr(arena), _ptr(out), _stream(stream)))
@@ -550,7 +562,7 @@ def decode_splits(t: Table, layer_begin: int, layer_end: int, q: torch.Tensor, n
     _need(q.is_contiguous() and q.numel() == nl * d.batch * d.n_q_heads * _q_width(d),
           "q must be contiguous, layers*B*Hq*width")
     _check_weights(t, nl, w_uk, w_uv)
-    _need(_nbytes(arena) >= table_query(t).arena_bytes, "arena smaller than arena_bytes")
+    _need(_nbytes(arena) >= t.arena_bytes, "arena smaller than arena_bytes")
     _check(load().kvk_decode_splits(
         t.handle, layer_begin, layer_end, _ptr(q), _dtype_code(q), n_stored, float(scale),
         _ptr(w_uk), _ptr(w_uv), _ptr(arena), _ptr(workspace), _nbytes(workspace), _stream(stream)))
@@ -570,7 +582,7 @@ def decode_merge(t: Table, layer_begin: int, layer_end: int, q: torch.Tensor, n_
           out.numel() == nl * d.batch * d.n_q_heads * _out_width(d),
           "out must be contiguous fp32, layers*B*Hq*width")
     _check_weights(t, nl, w_uk, w_uv)
-    _need(_nbytes(arena) >= table_query(t).arena_bytes, "arena smaller than arena_bytes")
+    _need(_nbytes(arena) >= t.arena_bytes, "arena smaller than arena_bytes")
     _check(load().kvk_decode_merge(
         t.handle, layer_begin, layer_end, _ptr(q), _dtype_code(q), n_stored, float(scale),
         _ptr(w_uk), _ptr(w_uv), _ptr(arena), _ptr(workspace), _nbytes(workspace), _ptr(out),
@@ -600,7 +612,7 @@ def debug_dequantize(t: Table, layer: int, n_stored: int, arena: torch.Tensor, k
         nk = nv = d.batch * d.n_kv_heads * n * d.head_dim
     _need(k_out.dtype == torch.float32 and v_out.dtype == torch.float32, "outputs must be fp32")
     _need(k_out.numel() >= nk and v_out.numel() >= nv, "outputs smaller than the dequantised cache")
-    _need(_nbytes(arena) >= table_query(t).arena_bytes, "arena smaller than arena_bytes")
+    _need(_nbytes(arena) >= t.arena_bytes, "arena smaller than arena_bytes")
     _check(load().kvk_debug_dequantize(t.handle, layer, n_stored, _ptr(arena), _ptr(k_out),
                                        _ptr(v_out), _stream(stream)))
 
