@@ -724,6 +724,21 @@ __device__ __forceinline__ const DecodeItem& item_at(const DecodeArgs& a, int i)
   else return a.items[i];
 }
 
+// The last item with wave_begin <= wave: 64 items per step, a lane each (one load for
+// up to 64 items, two for 4096; a binary search waits for each of its loads in turn).
+template <bool BATCHED>
+__device__ __forceinline__ int find_item(const DecodeArgs& a, int wave, int lane) {
+  int base = 0, len = a.n_items;
+  while (len > 1) {
+    const int stride = (len + 63) >> 6, k = lane * stride;
+    const bool before = k < len && item_at<BATCHED>(a, base + (k < len ? k : 0)).wave_begin <= wave;
+    const int at = (__popcll(__ballot(before)) - 1) * stride;  // lane 0's item always begins before
+    base += at;
+    len = min(stride, len - at);
+  }
+  return base;
+}
+
 template <int D, int QS, bool BATCHED>
 __global__ __launch_bounds__(256, 2) void gqa_decode_kernel(DecodeArgs a) {
   __shared__ uint32_t lds_meta[4][2 * D];  // per-wave metadata slot (KIVI32 8D bytes, GROUP64 4D)
@@ -735,12 +750,7 @@ __global__ __launch_bounds__(256, 2) void gqa_decode_kernel(DecodeArgs a) {
   if (wave >= a.total_waves) return;
   if constexpr (BATCHED)
     if (a.list_hdr[0] != kListMagic || a.list_hdr[1] != a.list_hash) return;  // not this call's list
-  int lo = 0, hi = a.n_items - 1;  // last item with wave_begin <= wave
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (item_at<BATCHED>(a, mid).wave_begin <= wave) lo = mid;
-    else hi = mid - 1;
-  }
+  const int lo = find_item<BATCHED>(a, wave, lane);
   const DecodeItem& it = item_at<BATCHED>(a, lo);
   const int local = wave - it.wave_begin;
   int chunk, unit;
@@ -782,12 +792,19 @@ __global__ __launch_bounds__(256, 2) void gqa_decode_kernel(DecodeArgs a) {
 }
 
 // Merge the splits of every output row by log-sum-exp, together with the bf16 tail
-// tokens (fewer than 32), which this kernel attends to directly: one wave per
-// (layer, b, head).
-template <int D, bool BATCHED>
+// tokens (fewer than 32), which this kernel attends to directly: WPR waves per (layer,
+// b, head), one, or the four of a workgroup where a row has many splits (each wave then
+// takes every fourth group of splits and a quarter of the tail's values).
+// Bound: the latency of a wave's few dependent steps, so each step issues all its loads
+// together.  7B shape, 28 layers x 8 sequences, 16 tail tokens: 24.8 -> 10 us against
+// one load at a time.
+// TAIL is false for calls without tail tokens: 40 registers instead of 102, so that twice
+// the waves share a SIMD.
+template <int D, bool BATCHED, int WPR, bool TAIL>
 __global__ __launch_bounds__(256) void gqa_combine_kernel(CombineArgs a) {
   const int lane = threadIdx.x & 63;
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int wslot = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform over the wave
+  const int row = WPR == 4 ? blockIdx.x : blockIdx.x * 4 + wslot, part = WPR == 4 ? wslot : 0;
   if (row >= a.n_rows) return;
   const int li = row / (a.B * a.Hq);
   const int rem = row % (a.B * a.Hq);
@@ -820,62 +837,140 @@ __global__ __launch_bounds__(256) void gqa_combine_kernel(CombineArgs a) {
   const float* base = a.ws + ws_off + (((int64_t)sidx * nsplit) * geff + slot) * (D + 4);
   const int64_t stride = (int64_t)geff * (D + 4);
 
-  // tail scores: lane t < ntail takes token t
+  // Tail scores: lane (t, half) takes half the channels of token t, all its loads in
+  // flight at once (a lane's serial walk over one token's channels made a 16-token tail
+  // most of this kernel's time).
   const uint8_t* tail = a.arena + tail_off + (int64_t)sidx * sbytes;
   float st = -INFINITY;
-  if (lane < a.ntail) {
-    const int64_t qoff = (int64_t)row * D;
+  if constexpr (TAIL) {
+    const int t = lane & 31, c1 = D / 2 * (lane >> 5);
     float acc = 0.0f;
-    for (int c0 = 0; c0 < D; c0 += 8) {
-      const uint4 kw = *reinterpret_cast<const uint4*>(tail + k_bf16_byte(D, lane, c0));
-      const uint32_t w[4] = {kw.x, kw.y, kw.z, kw.w};
-      float q[8];
-      if (a.q_f32) {
+    if (t < a.ntail) {
+      const int64_t qoff = (int64_t)row * D + c1;
+      uint4 kw[D / 16];
 #pragma unroll
-        for (int s = 0; s < 8; ++s) q[s] = static_cast<const float*>(a.q)[qoff + c0 + s];
-      } else {
+      for (int j = 0; j < D / 16; ++j) kw[j] = *reinterpret_cast<const uint4*>(tail + k_bf16_byte(D, t, c1 + 8 * j));
 #pragma unroll
-        for (int s = 0; s < 8; ++s) q[s] = bf16_to_f32(static_cast<const uint16_t*>(a.q)[qoff + c0 + s]);
-      }
+      for (int j = 0; j < D / 16; ++j) {
+        float q[8];
+        if (a.q_f32) {
+          const float4* qp = reinterpret_cast<const float4*>(static_cast<const float*>(a.q) + qoff + 8 * j);
+          const float4 v0 = qp[0], v1 = qp[1];
+          q[0] = v0.x; q[1] = v0.y; q[2] = v0.z; q[3] = v0.w;
+          q[4] = v1.x; q[5] = v1.y; q[6] = v1.z; q[7] = v1.w;
+        } else {
+          const uint4 v = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(a.q) + qoff + 8 * j);
+          const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        acc = fmaf(q[2 * p], __uint_as_float(w[p] << 16), acc);
-        acc = fmaf(q[2 * p + 1], __uint_as_float(w[p] & 0xffff0000u), acc);
+          for (int p = 0; p < 4; ++p) {
+            q[2 * p] = __uint_as_float(w[p] << 16);
+            q[2 * p + 1] = __uint_as_float(w[p] & 0xffff0000u);
+          }
+        }
+        const uint32_t w[4] = {kw[j].x, kw[j].y, kw[j].z, kw[j].w};
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+          acc = fmaf(q[2 * p], __uint_as_float(w[p] << 16), acc);
+          acc = fmaf(q[2 * p + 1], __uint_as_float(w[p] & 0xffff0000u), acc);
+        }
       }
     }
-    st = acc * a.scale_log2;
+    acc += __shfl_xor(acc, 32);
+    if (t < a.ntail) st = acc * a.scale_log2;  // both halves hold the token's score
   }
+
+  // Split weights: lane s holds split s0 + s (m, l).
   float mstar = st;
-  for (int s = lane; s < nlive; s += 64) mstar = fmaxf(mstar, base[s * stride + D]);
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) mstar = fmaxf(mstar, __shfl_xor(mstar, off));
-  constexpr int PER = D / 64;
+  float ms = -INFINITY, ls = 0.0f;
+  for (int s0 = 0; s0 < nlive; s0 += 64) {
+    ms = -INFINITY;
+    if (s0 + lane < nlive) {
+      const float2 ml = *reinterpret_cast<const float2*>(base + (s0 + lane) * stride + D);
+      ms = ml.x, ls = ml.y;
+    }
+    mstar = fmaxf(mstar, ms);
+  }
+  mstar = rows_max(max16(mstar));
+  // lane e holds channels PER e .. PER e + PER - 1
+  constexpr int PER = D / 64, kAhead = 4;
   float acc[PER];
 #pragma unroll
   for (int e = 0; e < PER; ++e) acc[e] = 0.0f;
   float lsum = 0.0f;
-  for (int s = 0; s < nlive; ++s) {
-    const float* p = base + s * stride;
-    const float ms = p[D];
-    const float w = (ms == -INFINITY) ? 0.0f : exp2f(ms - mstar);
-    lsum = fmaf(w, p[D + 1], lsum);
+  for (int s0 = 0; s0 < nlive; s0 += 64) {
+    if (nlive > 64) {  // uniform; one pass keeps what it read above
+      ms = -INFINITY;
+      if (s0 + lane < nlive) {
+        const float2 ml = *reinterpret_cast<const float2*>(base + (s0 + lane) * stride + D);
+        ms = ml.x, ls = ml.y;
+      }
+    }
+    const float w = ms == -INFINITY ? 0.0f : exp2f(ms - mstar);  // 0 past the live splits
+    lsum = fmaf(w, ms == -INFINITY ? 0.0f : ls, lsum);
+    const int n = min(64, nlive - s0);
+    for (int s = kAhead * part; s < n; s += kAhead * WPR) {  // kAhead splits' loads in flight
+      float p[kAhead][PER];
 #pragma unroll
-    for (int e = 0; e < PER; ++e) acc[e] = fmaf(w, p[lane + 64 * e], acc[e]);
-  }
-  const float pt = (st == -INFINITY) ? 0.0f : exp2f(st - mstar);
-  for (int t = 0; t < a.ntail; ++t) {
-    const float w = __shfl(pt, t);
-    lsum += w;
+      for (int u = 0; u < kAhead; ++u) {
+        const float* src = base + (s0 + min(s + u, n - 1)) * stride + PER * lane;
 #pragma unroll
-    for (int e = 0; e < PER; ++e) {
-      const uint16_t vb = *reinterpret_cast<const uint16_t*>(tail + v_bf16_byte(D, t, lane + 64 * e));
-      acc[e] = fmaf(w, bf16_to_f32(vb), acc[e]);
+        for (int e = 0; e < PER; ++e) p[u][e] = src[e];
+      }
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        if (s + u < n) {  // uniform
+          const float wu = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), s + u));
+#pragma unroll
+          for (int e = 0; e < PER; ++e) acc[e] = fmaf(wu, p[u][e], acc[e]);
+        }
+      }
     }
   }
-  const float inv = lsum > 0.0f ? 1.0f / lsum : 0.0f;
-  float* o = a.out + (int64_t)row * D;
+  const float pt = st == -INFINITY ? 0.0f : exp2f(st - mstar);
+  if (lane < 32) lsum += pt;
+  lsum = rows_sum(sum16(lsum));
+  if constexpr (TAIL) {
+    // a channel's values sit in four pieces of 8 tokens, 16 (s/4) + 4 kg + s%4
+    constexpr int NK = 4 / WPR;
+    uint4 vw[PER][NK];
 #pragma unroll
-  for (int e = 0; e < PER; ++e) o[lane + 64 * e] = acc[e] * inv;
+    for (int e = 0; e < PER; ++e)
+#pragma unroll
+      for (int k = 0; k < NK; ++k)
+        if (4 * (part + k) < a.ntail)  // uniform: a piece's first token is 4 kg
+          vw[e][k] = *reinterpret_cast<const uint4*>(tail + v_bf16_byte(D, 4 * (part + k), PER * lane + e));
+#pragma unroll
+    for (int k = 0; k < NK; ++k)
+#pragma unroll
+      for (int s = 0; s < 8; ++s) {
+        const int t = 16 * (s >> 2) + 4 * (part + k) + (s & 3);
+        if (t < a.ntail) {  // uniform; slots past the tail hold anything
+          const float wt = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(pt), t));
+#pragma unroll
+          for (int e = 0; e < PER; ++e) {
+            const uint32_t w4[4] = {vw[e][k].x, vw[e][k].y, vw[e][k].z, vw[e][k].w};
+            const uint32_t x = w4[s >> 1];
+            acc[e] = fmaf(wt, __uint_as_float(s & 1 ? x & 0xffff0000u : x << 16), acc[e]);
+          }
+        }
+      }
+  }
+  if constexpr (WPR == 4) {
+    __shared__ float red[3][D];
+    if (part > 0) {
+#pragma unroll
+      for (int e = 0; e < PER; ++e) red[part - 1][PER * lane + e] = acc[e];
+    }
+    __syncthreads();
+    if (part > 0) return;
+#pragma unroll
+    for (int e = 0; e < PER; ++e)
+      acc[e] += red[0][PER * lane + e] + (red[1][PER * lane + e] + red[2][PER * lane + e]);
+  }
+  const float inv = lsum > 0.0f ? 1.0f / lsum : 0.0f;
+  float* o = a.out + (int64_t)row * D + PER * lane;
+#pragma unroll
+  for (int e = 0; e < PER; ++e) o[e] = acc[e] * inv;
 }
 
 }  // namespace
@@ -897,6 +992,7 @@ struct DecodePlan {
   int head_dim;
   bool any_blocks;
   bool batched;
+  int max_splits;  // of any item
   std::vector<uint8_t> list;  // the host image of the work list (per-sequence plans)
   uint64_t hash;              // its hash (FNV-1a over the list after the header)
 };
@@ -1009,7 +1105,7 @@ kvk_status prepare(const kvk_table* t, int32_t l0, int32_t l1, const void* q, in
   ca.nbf = nbf;
   ca.map = nullptr;
 
-  const int64_t split_target = gqa_split_target(t, l0, l1);
+  const GqaSplitRule split_rule = gqa_split_rule(t, l0, l1);
   // One work item per distinct anchor read by the range (§2.1 depth sharing): per
   // anchor for all sequences, or per (sequence, anchor) under per-sequence plans.
   SmallVec<DecodeItem, kMaxItems> items;
@@ -1033,7 +1129,7 @@ kvk_status prepare(const kvk_table* t, int32_t l0, int32_t l1, const void* q, in
         it.bits = s->bits[anc];
         it.q_layer0 = rb - l0;
         it.geff = G * (re - rb);
-        it.split_blocks = gqa_item_split_blocks(s, anc, l0, l1, nbf_split, split_target);
+        it.split_blocks = gqa_item_split_blocks(s, anc, l0, l1, nbf_split, split_rule);
         it.nsplit = n_splits(nbf_split, it.split_blocks);
         it.nchp = gqa_chunk_waves((it.geff + 15) / 16);
         it.b0 = b0;
@@ -1072,8 +1168,10 @@ kvk_status prepare(const kvk_table* t, int32_t l0, int32_t l1, const void* q, in
   SmallVec<DecodeItem, kMaxItems> sorted;
   sorted.resize(n_it);
   int64_t waves = 0;
+  P.max_splits = 0;
   for (int k = 0; k < n_it; ++k) {
     DecodeItem it = items[order[k]];
+    P.max_splits = std::max(P.max_splits, it.nsplit);
     waves = (waves + 3) / 4 * 4;  // a chunk group never straddles a workgroup
     it.wave_begin = (int32_t)waves;
     int64_t units = (int64_t)it.nb * d.n_kv_heads * it.nsplit;
@@ -1175,15 +1273,25 @@ kvk_status launch_d1(const DecodePlan& P, hipStream_t st) {
   return KVK_OK;
 }
 
-kvk_status launch_c1(const DecodePlan& P, hipStream_t st) {
-  const unsigned grid = (unsigned)((P.c1.n_rows + 3) / 4);
-  if (P.head_dim == 128) {
-    if (P.batched) hipLaunchKernelGGL((gqa_combine_kernel<128, true>), dim3(grid), dim3(256), 0, st, P.c1);
-    else hipLaunchKernelGGL((gqa_combine_kernel<128, false>), dim3(grid), dim3(256), 0, st, P.c1);
+template <int D, bool BATCHED>
+void launch_c1_kernel(const DecodePlan& P, hipStream_t st) {
+  // Four waves per row for many splits: 57 splits of 64 rows 8.5 -> 5.7 us, but 16
+  // splits of 784 rows 6.1 -> 7.1 us (a quarter of the steps against four times the
+  // waves and a barrier).
+  const bool four = P.max_splits > 24;
+  const dim3 g((unsigned)(four ? P.c1.n_rows : (P.c1.n_rows + 3) / 4)), b(256);
+  if (P.c1.ntail > 0) {
+    if (four) hipLaunchKernelGGL((gqa_combine_kernel<D, BATCHED, 4, true>), g, b, 0, st, P.c1);
+    else hipLaunchKernelGGL((gqa_combine_kernel<D, BATCHED, 1, true>), g, b, 0, st, P.c1);
   } else {
-    if (P.batched) hipLaunchKernelGGL((gqa_combine_kernel<64, true>), dim3(grid), dim3(256), 0, st, P.c1);
-    else hipLaunchKernelGGL((gqa_combine_kernel<64, false>), dim3(grid), dim3(256), 0, st, P.c1);
+    if (four) hipLaunchKernelGGL((gqa_combine_kernel<D, BATCHED, 4, false>), g, b, 0, st, P.c1);
+    else hipLaunchKernelGGL((gqa_combine_kernel<D, BATCHED, 1, false>), g, b, 0, st, P.c1);
   }
+}
+
+kvk_status launch_c1(const DecodePlan& P, hipStream_t st) {
+  if (P.head_dim == 128) P.batched ? launch_c1_kernel<128, true>(P, st) : launch_c1_kernel<128, false>(P, st);
+  else P.batched ? launch_c1_kernel<64, true>(P, st) : launch_c1_kernel<64, false>(P, st);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(KVK_ERR_DEVICE, "combine launch: %s", hipGetErrorString(e));
   return KVK_OK;

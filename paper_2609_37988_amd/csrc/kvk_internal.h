@@ -110,7 +110,12 @@ inline int32_t ring_depth_for(int32_t bits) { return gqa_ring_depth(bits); }
 // the capacity covers every n_stored (the count itself is not monotone in the
 // length).  `waves` D1 waves read each split (an item's chunk waves), so its target
 // and its bounds are that many times the per-wave ones.
-int32_t split_blocks_for(int32_t bits, int32_t qscheme, int32_t head_dim, int32_t n_blocks, int64_t target_bytes,
+struct GqaSplitRule {
+  int64_t bytes;   // cache bytes per D1 wave the launch aims at
+  int64_t round;   // > 0: a launch of one round of waves, its cost per wave (table.cpp)
+  int32_t nb_cap;  // full-block capacity of its streams
+};
+int32_t split_blocks_for(int32_t bits, int32_t qscheme, int32_t head_dim, int32_t n_blocks, const GqaSplitRule& rule,
                          int32_t waves, int32_t* count_bound = nullptr);
 // D1 waves per (stream, split) of an item whose anchor's readers give nch 16-row
 // query chunks: 1, 2, or a multiple of 4 (up to 4 share a workgroup, more fill
@@ -119,9 +124,10 @@ constexpr int32_t gqa_chunk_waves(int32_t nch) { return nch == 1 ? 1 : (nch == 2
 // Full blocks per split of the D1 item of `anchor` read by the layers of [l0, l1)
 // in table s (split_blocks_for with the item's chunk waves in one workgroup).
 int32_t gqa_item_split_blocks(const kvk_table* s, int32_t anchor, int32_t l0, int32_t l1, int32_t n_blocks,
-                              int64_t target_bytes, int32_t* count_bound = nullptr);
-// Bytes per D1 split for a decode over layers [l0, l1) of a GQA table (see table.cpp).
-int64_t gqa_split_target(const kvk_table* t, int32_t l0, int32_t l1);
+                              const GqaSplitRule& rule, int32_t* count_bound = nullptr);
+// How a decode over layers [l0, l1) of a GQA table splits its streams; computed from
+// the capacity, so that the splits' partials are bounded for every n_stored.
+GqaSplitRule gqa_split_rule(const kvk_table* t, int32_t l0, int32_t l1);
 
 // Bytes at the head of the workspace that hold the device-side work list of a
 // decode over [l0, l1) of a per-sequence table (decode.hip).

@@ -6,6 +6,7 @@
 // layer owns a cache or inherits from the nearest anchor before it).  The
 // storage accounting follows App. C.3.  Nothing in this file launches work on a
 // device; it only asks the HIP runtime whether a buffer is GPU memory.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -58,7 +59,7 @@ int64_t gqa_block_bytes(int32_t head_dim, int32_t bits, int32_t qscheme) {
   return 8 * D * bits + 128;                      // codes + bf16 row scales
 }
 
-int64_t gqa_split_target(const kvk_table* t, int32_t l0, int32_t l1) {
+static int64_t gqa_split_bytes(const kvk_table* t, int32_t l0, int32_t l1) {
   // A wave pays its start (query, filling its prefetch ring) and its split
   // partial once, so splits are as long as the launch allows while it still has
   // about kSplitWaves waves: two rounds of the D1 wave slots of an MI355X (256 CUs
@@ -82,9 +83,117 @@ int64_t gqa_split_target(const kvk_table* t, int32_t l0, int32_t l1) {
   return total / kSplitWaves;  // clamped per precision by split_blocks_for
 }
 
-int32_t split_blocks_for(int32_t bits, int32_t qscheme, int32_t head_dim, int32_t n_blocks, int64_t target_bytes,
+// Time of a block of each precision for a wave of a full launch (two waves per SIMD),
+// in sixteenths of a 4-bit block's (7B and 14B stacks: about 3, 2.2, 2 and 2 us).
+static int32_t round_cost(int32_t bits) { return bits == 16 ? 24 : (bits == 8 ? 18 : 16); }
+
+// Full blocks per split in a one-round launch of cost `round` per wave: at least one
+// pass of the kernel's ring, and at most kRoundSplits splits per stream.
+constexpr int64_t kRoundWaves = 2048;  // D1 wave slots of an MI355X (256 CUs x 8 waves)
+constexpr int64_t kRoundSplits = 64;
+static int64_t round_target(int32_t bits, int64_t round, int64_t n_blocks) {
+  const int64_t least = std::max<int64_t>(ring_depth_for(bits), (n_blocks + kRoundSplits - 1) / kRoundSplits);
+  return std::max(least, round / round_cost(bits));
+}
+
+// D1 waves of one (stream, split) of an anchor's item, and its query rows.
+static int32_t gqa_item_rows(const kvk_table* s, int32_t anchor, int32_t l0, int32_t l1) {
+  const int32_t G = s->d.n_q_heads / s->d.n_kv_heads;
+  const int32_t rb = anchor > l0 ? anchor : l0;
+  const int32_t re = s->next_anchor[anchor] < l1 ? s->next_anchor[anchor] : l1;
+  return G * (re - rb);
+}
+
+// The cost per wave of a launch that the byte rule would leave with fewer waves than
+// slots, 0 for any other launch.  Such a launch lasts as long as its longest wave, so
+// its streams are cut into splits of about equal time, as short as keeps every wave
+// in the first round (a wave more than the slots starts after a whole first wave has
+// ended).  Measured at batch 1, 7B shape, 4097 tokens, D1: bf16 whole streams 150 us,
+// 64-block splits 84, 16-block splits (896 waves) 39; int4 whole 127, 64 blocks 67, 8
+// blocks (1792 waves) 22; 14B shape, 8192 tokens, int8: 32-block splits (3072 waves)
+// 145 us, 48 (2304 waves) 162, 64 (1536) 147, whole 251; eight 7B sequences with their
+// own mixed plans, 6000 tokens: 64-block splits of every precision (1824 waves) 203 us
+// against 250 with the byte rule.  Launches that fill the slots keep the byte rule:
+// several rounds of waves balance themselves (128k eviction stack, 4700 waves: 1104 us
+// against 1138 in one round; 14B mixed stack at batch 8: 610 against 713).
+static int64_t gqa_round_cost(const kvk_table* t, int32_t l0, int32_t l1, const GqaSplitRule& bytes) {
+  const int64_t nb = t->nb_cap;
+  if (nb < 1) return 0;
+  int64_t units[4] = {0, 0, 0, 0};  // chunk waves over all streams, by precision
+  int64_t byte_waves = 0;
+  static constexpr int32_t kBits[4] = {16, 8, 4, 2};
+  const size_t n_seq = t->seq.empty() ? 1 : t->seq.size();
+  for (size_t i = 0; i < n_seq; ++i) {
+    const kvk_table* s = t->seq.empty() ? t : t->seq[i];
+    int32_t last = -1;  // a range's anchors come in order
+    for (int l = l0; l < l1; ++l) {
+      const int32_t a = s->info.anchor_of[l];
+      if (a == last) continue;
+      last = a;
+      const int64_t waves = (int64_t)s->d.batch * s->d.n_kv_heads *
+                            gqa_chunk_waves((gqa_item_rows(s, a, l0, l1) + 15) / 16);
+      for (int k = 0; k < 4; ++k)
+        if (s->bits[a] == kBits[k]) units[k] += waves;
+      byte_waves += waves * n_splits((int32_t)nb, gqa_item_split_blocks(s, a, l0, l1, (int32_t)nb, bytes));
+      if (byte_waves >= kRoundWaves) return 0;
+    }
+  }
+  int64_t cost = 0;
+  for (int k = 0; k < 4; ++k) cost += units[k] * nb * round_cost(kBits[k]);
+  for (int64_t round = std::max<int64_t>(cost / kRoundWaves, 1);; round += round / 16 + 1) {
+    int64_t waves = 0;
+    for (int k = 0; k < 4; ++k) {
+      const int64_t target = round_target(kBits[k], round, nb);
+      waves += units[k] * ((nb + target - 1) / target);
+    }
+    if (waves <= kRoundWaves) return round;  // whole streams at the latest: units <= byte_waves
+  }
+}
+
+// Bytes of the split partials of a decode over [l0, l1) by a split rule: per query row
+// (layer, b, head) and split (o[d_h], m, l, 2 pad) in fp32, the splits of every
+// n_stored up to the capacity (full blocks; the merge kernel attends to the tail).
+static int64_t gqa_partial_bytes(const kvk_table* t, int32_t l0, int32_t l1, const GqaSplitRule& rule) {
+  const int32_t G = t->d.n_q_heads / t->d.n_kv_heads;
+  const size_t n_seq = t->seq.empty() ? 1 : t->seq.size();
+  int64_t floats = 0;
+  for (size_t i = 0; i < n_seq; ++i) {
+    const kvk_table* s = t->seq.empty() ? t : t->seq[i];
+    for (int l = l0; l < l1; ++l) {
+      int32_t bound = 0;
+      gqa_item_split_blocks(s, s->info.anchor_of[l], l0, l1, t->nb_cap, rule, &bound);
+      floats += (int64_t)s->d.batch * s->d.n_kv_heads * G * bound * (t->d.head_dim + 4);
+    }
+  }
+  return round256(floats * (int64_t)sizeof(float));
+}
+
+GqaSplitRule gqa_split_rule(const kvk_table* t, int32_t l0, int32_t l1) {
+  GqaSplitRule r;
+  r.nb_cap = t->nb_cap;
+  r.bytes = gqa_split_bytes(t, l0, l1);
+  r.round = 0;
+  r.round = gqa_round_cost(t, l0, l1, r);
+  // A workspace of the whole range serves its parts: a part whose partials would need
+  // more keeps the byte rule.
+  if (r.round > 0 && (l0 > 0 || l1 < t->d.n_layers) &&
+      gqa_batched_list_bytes(t, l0, l1) + gqa_partial_bytes(t, l0, l1, r) > t->info.workspace_bytes)
+    r.round = 0;
+  return r;
+}
+
+int32_t split_blocks_for(int32_t bits, int32_t qscheme, int32_t head_dim, int32_t n_blocks, const GqaSplitRule& rule,
                          int32_t waves, int32_t* count_bound) {
-  // target_bytes of cache per wave (gqa_split_target); the stream's blocks are
+  const int64_t nr = ring_depth_for(bits);
+  const int64_t nb = n_blocks > 0 ? n_blocks : 1;
+  if (rule.round > 0) {  // a launch of one round: equal times per wave
+    const int64_t target = round_target(bits, rule.round, rule.nb_cap);
+    const int64_t nsplit = (nb + target - 1) / target;
+    if (count_bound) *count_bound = (int32_t)nsplit;  // grows with nb, as below
+    return (int32_t)(((nb + nsplit - 1) / nsplit + nr - 1) / nr * nr);
+  }
+  int64_t target_bytes = rule.bytes;
+  // target_bytes of cache per wave (gqa_split_bytes); the stream's blocks are
   // divided evenly so that no split is a short remainder, in a multiple of the
   // decode kernel's prefetch depth so that only a stream's last split runs past
   // its end.  A split read by `waves` chunk waves (an anchor with many reader rows)
@@ -94,7 +203,6 @@ int32_t split_blocks_for(int32_t bits, int32_t qscheme, int32_t head_dim, int32_
   // 127 KiB of partials per split and stream; 357 MB of partials per step with
   // per-wave splits, 97 MB with 4x longer ones).
   const int64_t bb = gqa_block_bytes(head_dim, bits, qscheme);
-  const int64_t nr = ring_depth_for(bits);
   // The 8- and 16-bit paths stream: splits between 1 and 16 MiB.  The 2- and 4-bit
   // paths are bound by their unpacking, not by the stream, so longer splits do not
   // pay there (14B eviction stack: 1 MiB 1.14 ms, 1.1 MiB 1.17 ms); their splits are
@@ -114,7 +222,6 @@ int32_t split_blocks_for(int32_t bits, int32_t qscheme, int32_t head_dim, int32_
   target_bytes *= w * (bits == 16 ? 8 : (bits <= 4 ? 2 : 1));
   int64_t target = (target_bytes < lo ? lo : (target_bytes > hi ? hi : target_bytes)) / bb;
   if (target < nr) target = nr;
-  const int64_t nb = n_blocks > 0 ? n_blocks : 1;
   int64_t nsplit = (nb + target - 1) / target;
   // The 2- and 4-bit items take one split fewer when the longer splits stay within
   // the clamp: the split count rounded down instead of up keeps a launch within one
@@ -136,19 +243,15 @@ int32_t split_blocks_for(int32_t bits, int32_t qscheme, int32_t head_dim, int32_
 }
 
 int32_t gqa_item_split_blocks(const kvk_table* s, int32_t anchor, int32_t l0, int32_t l1, int32_t n_blocks,
-                              int64_t target_bytes, int32_t* count_bound) {
-  const int32_t G = s->d.n_q_heads / s->d.n_kv_heads;
-  const int32_t rb = anchor > l0 ? anchor : l0;
-  const int32_t re = s->next_anchor[anchor] < l1 ? s->next_anchor[anchor] : l1;
-  const int32_t nch = (G * (re - rb) + 15) / 16;
+                              const GqaSplitRule& rule, int32_t* count_bound) {
+  const int32_t nch = (gqa_item_rows(s, anchor, l0, l1) + 15) / 16;
   // Only the chunk waves of one workgroup (up to 4) lengthen the split: the several
   // workgroups of a larger unit drift apart over a long split and then read it from
   // HBM again (one int4 anchor for 48 layers at 14B, 16 chunk waves: FETCH 1.38x the
   // cache bytes with per-wave splits, 1.19x with 4x longer ones, 1.41x with 8x, 1.69x
   // with 16x).
   const int32_t w = gqa_chunk_waves(nch);
-  return split_blocks_for(s->bits[anchor], s->d.qscheme, s->d.head_dim, n_blocks, target_bytes, w < 4 ? w : 4,
-                          count_bound);
+  return split_blocks_for(s->bits[anchor], s->d.qscheme, s->d.head_dim, n_blocks, rule, w < 4 ? w : 4, count_bound);
 }
 
 int64_t mla_block_bytes(int32_t W, int32_t bits, int32_t qscheme) {
@@ -466,18 +569,12 @@ extern "C" kvk_status kvk_workspace_bytes(const kvk_table* t, int32_t l0, int32_
     *out = (size_t)ws.total;
     return KVK_OK;
   }
-  if (!t->seq.empty()) {
-    // The device-side work list, then GQA: every sequence's split partials (each
-    // sized with its own, smaller, split target: the batch's longer splits need no
-    // more); MLA: every sequence's own workspace, one after the other.
-    size_t total;
-    if (d.kind == KVK_MLA) {
-      MlaSeqList L;
-      if (kvk_status st = mla_seq_list(t, l0, l1, L, false)) return st;
-      total = (size_t)L.bytes;
-    } else {
-      total = (size_t)gqa_batched_list_bytes(t, l0, l1);
-    }
+  if (!t->seq.empty() && d.kind == KVK_MLA) {
+    // The device-side work list, then every sequence's own workspace, one after the
+    // other.
+    MlaSeqList L;
+    if (kvk_status st = mla_seq_list(t, l0, l1, L, false)) return st;
+    size_t total = (size_t)L.bytes;
     for (const kvk_table* s : t->seq) {
       size_t one = 0;
       const kvk_status st = kvk_workspace_bytes(s, l0, l1, &one);
@@ -487,18 +584,7 @@ extern "C" kvk_status kvk_workspace_bytes(const kvk_table* t, int32_t l0, int32_
     *out = total;
     return KVK_OK;
   }
-  const int32_t G = d.n_q_heads / d.n_kv_heads;
-  // Split partials: per query row (layer, b, head) and split, (o[d_h], m, l, 2 pad) in fp32.
-  const int32_t nblk = t->nb_cap;  // full blocks; the tail is merged by the combine kernel
-  const int64_t target = gqa_split_target(t, l0, l1);
-  size_t floats = 0;
-  for (int l = l0; l < l1; ++l) {
-    const int32_t a = t->info.anchor_of[l];
-    int32_t bound = 0;  // the splits of every n_stored up to the capacity
-    gqa_item_split_blocks(t, a, l0, l1, nblk, target, &bound);
-    floats += (size_t)d.batch * d.n_kv_heads * G * bound * (d.head_dim + 4);
-  }
-  *out = (size_t)round256((int64_t)(floats * sizeof(float)));
+  *out = (size_t)(gqa_batched_list_bytes(t, l0, l1) + gqa_partial_bytes(t, l0, l1, gqa_split_rule(t, l0, l1)));
   return KVK_OK;
 }
 

@@ -194,6 +194,20 @@ def test_many_splits(bits, n):
     assert rel_err(out, ref) <= TOL
 
 
+@pytest.mark.parametrize("bits,D,n", [(4, 64, 20017), (16, 128, 4127), (2, 128, 257), (8, 64, 8191)])
+def test_split_merge(bits, D, n):
+    """Launches of one round: 53 splits with a 17-token tail and 64 with 31 (four merge waves a row),
+    22 ring passes and a full tail, one pass and one token."""
+    say(f"case split-merge bits={bits} D={D} n={n}")
+    c = Case(1, 4, 1, D, 1, n, [(0, bits)])
+    k, v = synth.kv_random(190 + bits, 1, 1, n, D)
+    c.compress(0, k.cuda(), v.cuda(), n)
+    q = synth.q_random(191, 1, 1, 4, D, dtype=torch.float32)
+    out = _np(c.decode(q.cuda(), n, 0.11))
+    ref = _oracle_out(c, {0: (_np(k), _np(v))}, q, n, 0.11)
+    assert rel_err(out, ref) <= TOL
+
+
 def test_workspace_covers_every_stored_length():
     """The split count is not monotone in the stored length (rounding a split up to
     whole ring passes can save one: a 4-bit stream with 25-block splits takes 8 splits

@@ -473,3 +473,22 @@ def test_batched_mla_table_accounting_matches_oracle():
     # the work list (rows and items, a few KiB) at the head, then every sequence's own
     assert one_ws < kvk.workspace_bytes(t, 0, 3) <= one_ws + (16 << 10)
     assert kvk.read_bytes(t, 0, 3, 250) == OP.read_bytes_batched(od, oplans, 0, 3, 250)
+
+
+@pytest.mark.parametrize("L,B,hkv,G,T", [(1, 1, 1, 4, 20000), (28, 1, 4, 7, 4097), (48, 4, 8, 5, 700), (48, 32, 8, 5, 8192),
+                                         (2, 32, 8, 8, 131072)])
+def test_gqa_workspace_of_parts(L, B, hkv, G, T):
+    """A launch of one round holds at most 2048 waves of 16 rows (each a partial of d_h + 4 floats); the
+    workspace of the whole layer range serves every part of it unless the byte rule's splits (1 MiB and
+    128 KiB a wave at the least) already needed more."""
+    D = 128
+    plan = kvk.make_plan([(0, (16, 4, 2, 8)[i % 4]) if i % 3 == 0 else (1, 16) for i in range(L)])
+    t = kvk.layer_table(kvk.make_dims(kvk.GQA, L, hkv * G, hkv, D, batch=B, max_tokens=T), plan)
+    whole = kvk.workspace_bytes(t, 0, L)
+    rows = L * B * hkv * G
+    bound = max(2048 * 16, rows * (T // 32 * 32 * 4 * D // (128 << 10) + 1)) * (D + 4) * 4 + 256
+    assert rows * (D + 4) * 4 <= whole <= bound
+    for l in range(0, L, 3):
+        part = kvk.workspace_bytes(t, l, l + 1)
+        one = B * hkv * G * (D + 4) * 4
+        assert one <= part <= max(whole, one * (T * 4 * D // (128 << 10) + 2))
