@@ -22,6 +22,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "kvk_device.h"
 #include "kvk_internal.h"
@@ -32,7 +33,7 @@ namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kWin = 32;      // observation window
-constexpr int kChunk = 2048;  // tokens per workgroup in the score passes
+constexpr int kChunk = 2048;  // most tokens per workgroup in the score passes
 constexpr int kMaxG = 8;      // query heads per KV head
 
 struct SnapArgs {
@@ -43,6 +44,7 @@ struct SnapArgs {
   float* imp;         // [BH][n]
   int32_t* keep;      // [BH][keep_n]
   int32_t n, P, R, Hkv, Hq, keep_n;
+  int32_t chunk;      // tokens per workgroup, a multiple of 128
   float scale_log2;
 };
 
@@ -51,127 +53,155 @@ __device__ __forceinline__ f4 mfma_bf16(bf16x8 a, bf16x8 b, f4 c) {
 }
 
 // PASS 0: per-chunk row statistics.  PASS 1: importance of every token.
-// Wave w of the workgroup takes token tiles of 16 at chunk offsets 16 w, 16 w + 64, ..
-// S^T tile layout (A = 16 query rows, B = 16 tokens): lane (token i16, row group kg)
-// holds rows 4 kg .. 4 kg + 3 of its token.
+// Wave w of the workgroup takes 32 tokens (two MFMA tiles, sharing each read of the
+// queries) at chunk offsets 32 w, 32 w + 128, ..  S tile layout (A = 16 tokens, B = 16
+// query rows): lane (row i16, kg) holds tokens 4 kg .. 4 kg + 3 of its row, so a row's
+// running maximum and sum are one register each and eight scores share one rescale.
+// Bound: about evenly the exponentials (four cycles each per SIMD lane group), the
+// products and, for long prompts, the key reads.  B 4 x 8 KV heads x 131072 positions,
+// 5 heads a group: see snapkv_select's figures at launch_scores.
 template <int D, int PASS, int G>
-__global__ __launch_bounds__(256) void snap_scores_kernel(SnapArgs a) {
+__global__ __launch_bounds__(256, G <= 5 ? 3 : 2) void snap_scores_kernel(SnapArgs a) {
   constexpr int RT = 2 * G;  // row tiles of 16
   constexpr int R = 32 * G;  // window rows of the KV head
   constexpr int PQ = D + 8;  // LDS row pitch (bf16): consecutive rows 16 bytes apart in bank space
+  constexpr int NJ = D / 32;
   extern __shared__ uint16_t qs[];  // [R][PQ], sized by the launch
-  __shared__ float red[4][R][2];
+  __shared__ float red[PASS == 0 ? 4 : 1][PASS == 0 ? R : 1][2];
   const int tid = threadIdx.x, lane = tid & 63, i16 = lane & 15, kg = lane >> 4;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int bh = blockIdx.y, p = blockIdx.x;
   const int b = bh / a.Hkv, h = bh % a.Hkv;
   const uint16_t* qb = a.q + (int64_t)(b * a.Hq + h * G) * kWin * D;
-  for (int c = tid; c < R * (D / 8); c += 256) {
-    const int r = c / (D / 8), o = 8 * (c % (D / 8));
-    *reinterpret_cast<uint4*>(&qs[r * PQ + o]) = *reinterpret_cast<const uint4*>(qb + (int64_t)r * D + o);
+  // The queries carry the scale's sign (exact), so that a row's largest product gives
+  // its largest score.
+  const uint32_t sign = a.scale_log2 < 0.0f ? 0x80008000u : 0u;
+  const float c = fabsf(a.scale_log2);
+  for (int i = tid; i < R * (D / 8); i += 256) {
+    const int r = i / (D / 8), o = 8 * (i % (D / 8));
+    u4v w = *reinterpret_cast<const u4v*>(qb + (int64_t)r * D + o);
+    w ^= sign;
+    *reinterpret_cast<u4v*>(&qs[r * PQ + o]) = w;
   }
   __syncthreads();
 
-  float m[RT][4], l[RT][4];  // PASS 0: running max / sum of 2^(s - max)
-  float sm[RT][4], sl[RT][4];  // PASS 1: M and 1/L of the lane's rows
+  float m[RT], l[RT];  // PASS 0: running max (scaled) and sum of 2^(s - max); PASS 1: M and 1/L
 #pragma unroll
-  for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      if constexpr (PASS == 0) {
-        m[rt][e] = -INFINITY;
-        l[rt][e] = 0.0f;
-      } else {
-        const int r = 16 * rt + 4 * kg + e;
-        const float* st = a.stats + ((int64_t)bh * R + r) * 2;
-        sm[rt][e] = st[0];
-        sl[rt][e] = st[1];
-      }
+  for (int rt = 0; rt < RT; ++rt) {
+    if constexpr (PASS == 0) {
+      m[rt] = -INFINITY;
+      l[rt] = 0.0f;
+    } else {
+      const float2 st = *reinterpret_cast<const float2*>(a.stats + ((int64_t)bh * R + 16 * rt + i16) * 2);
+      m[rt] = st.x;
+      l[rt] = st.y;
     }
+  }
 
-  const int t0 = p * kChunk, t1 = min(a.n, t0 + kChunk);
-  const uint16_t* kb = a.k + (int64_t)bh * a.n * D;
-  // The key operand of the next tile is loaded while the current one is computed.
-  bf16x8 kn[D / 32];
-  auto load_keys = [&](int t) {
+  const int t0 = p * a.chunk, t1 = min(a.n, t0 + a.chunk);
+  const uint16_t* kb = a.k + (int64_t)bh * a.n * D + 8 * kg;
+  // The key operands of the next tiles are loaded while the current ones are computed
+  // (past the chunk: its last token again, never used).
+  bf16x8 kn[2][NJ], kv[2][NJ];
+  auto load_keys = [&](int tt) {
 #pragma unroll
-    for (int j = 0; j < D / 32; ++j) {
-      if (t < t1) kn[j] = *reinterpret_cast<const bf16x8*>(kb + (int64_t)t * D + 32 * j + 8 * kg);
-      else kn[j] = bf16x8{};
+    for (int u = 0; u < 2; ++u) {
+      const u4v* kp = reinterpret_cast<const u4v*>(kb + (int64_t)min(tt + 16 * u + i16, t1 - 1) * D);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) kn[u][j] = bitcast<bf16x8>(__builtin_nontemporal_load(kp + 4 * j));
     }
   };
-  load_keys(t0 + 16 * wv + i16);
-  for (int tt = t0 + 16 * wv; tt < t1; tt += 64) {
-    const int t = tt + i16;
-    bf16x8 kv[D / 32];
+  // One step over the 32 tokens from tt: MASK where some row does not see all of them.
+  auto step = [&](int tt, auto masked) {
+    constexpr bool MASK = decltype(masked)::value;
+    float imp[8];
 #pragma unroll
-    for (int j = 0; j < D / 32; ++j) kv[j] = kn[j];
-    load_keys(t + 64);
-    float imp = 0.0f;
+    for (int e = 0; e < 8; ++e) imp[e] = 0.0f;
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
-      {
-        f4 acc = {0.f, 0.f, 0.f, 0.f};
+      f4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-        for (int j = 0; j < D / 32; ++j) {
-          const bf16x8 qa = *reinterpret_cast<const bf16x8*>(&qs[(16 * rt + i16) * PQ + 32 * j + 8 * kg]);
-          acc = mfma_bf16(qa, kv[j], acc);
+      for (int j = 0; j < NJ; ++j) {
+        const bf16x8 qa = *reinterpret_cast<const bf16x8*>(&qs[(16 * rt + i16) * PQ + 32 * j + 8 * kg]);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) acc[u] = mfma_bf16(kv[u][j], qa, acc[u]);
+      }
+      // token tt + 16 u + 4 kg + e is visible to window slot w up to n - 32 + w
+      const int last = a.n - kWin + 16 * (rt & 1) + i16;
+      const auto sees = [&](int e) { return !MASK || tt + 16 * (e >> 2) + 4 * kg + (e & 3) <= last; };
+      float x[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = acc[e >> 2][e & 3];
+      if constexpr (PASS == 0) {
+        float mx = sees(0) ? x[0] : -INFINITY;
+#pragma unroll
+        for (int e = 1; e < 8; ++e) mx = fmaxf(mx, sees(e) ? x[e] : -INFINITY);
+        const float mn = fmaxf(m[rt], MASK && mx == -INFINITY ? -INFINITY : mx * c);
+        const float base = MASK && mn == -INFINITY ? 0.0f : mn;  // nothing seen yet
+        float s[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float pe = __builtin_amdgcn_exp2f(fmaf(x[e], c, -base));
+          s[e] = sees(e) ? pe : 0.0f;
         }
+        const float sum = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+        l[rt] = fmaf(l[rt], __builtin_amdgcn_exp2f(m[rt] - base), sum);
+        m[rt] = mn;
+      } else {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int w = (16 * rt + 4 * kg + e) & (kWin - 1);  // window slot of the row (rows are head-major)
-          const bool vis = t < a.n && t <= a.n - kWin + w;
-          const float s = acc[e] * a.scale_log2;
-          if constexpr (PASS == 0) {
-            if (vis) {
-              if (s > m[rt][e]) {
-                l[rt][e] *= __builtin_amdgcn_exp2f(m[rt][e] - s);
-                m[rt][e] = s;
-              }
-              l[rt][e] += __builtin_amdgcn_exp2f(s - m[rt][e]);
-            }
-          } else {
-            if (vis) imp += __builtin_amdgcn_exp2f(s - sm[rt][e]) * sl[rt][e];
-          }
+        for (int e = 0; e < 8; ++e) {
+          const float pe = __builtin_amdgcn_exp2f(fmaf(x[e], c, -m[rt]));
+          imp[e] = fmaf(sees(e) ? pe : 0.0f, l[rt], imp[e]);
         }
       }
       __builtin_amdgcn_sched_barrier(0);  // one row tile's operands live at a time
     }
     if constexpr (PASS == 1) {
-      imp = rows_sum(imp);  // over the four row groups
-      if (kg == 0 && t < a.n) a.imp[(int64_t)bh * a.n + t] = imp;
+      // over the 16 rows of a tile; lane i16 < 8 of each group stores token 16 (i16/4) + 4 kg + i16%4
+      float v = 0.0f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float s = sum16(imp[e]);
+        v = i16 == e ? s : v;
+      }
+      const int t = tt + 16 * (i16 >> 2) + 4 * kg + (i16 & 3);
+      if (i16 < 8 && t < a.n) a.imp[(int64_t)bh * a.n + t] = v;
     }
+  };
+  if (t0 + 32 * wv < t1) load_keys(t0 + 32 * wv);
+  for (int tt = t0 + 32 * wv; tt < t1; tt += 128) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) kv[u][j] = kn[u][j];
+    load_keys(tt + 128);
+    if (tt + 31 <= a.n - kWin) step(tt, std::false_type{});
+    else step(tt, std::true_type{});
   }
 
   if constexpr (PASS == 0) {
-    // over the 16 tokens of a row group (lanes i16), then over the 4 waves
+    // over the four token groups of a row (lanes i16 + 16 kg), then over the 4 waves
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
-      {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float M = max16(m[rt][e]);
-          const float x = M == -INFINITY ? 0.0f : l[rt][e] * __builtin_amdgcn_exp2f(m[rt][e] - M);
-          const float L = sum16(x);
-          if (i16 == 0) {
-            red[wv][16 * rt + 4 * kg + e][0] = M;
-            red[wv][16 * rt + 4 * kg + e][1] = L;
-          }
-        }
+      const float M = rows_max(m[rt]);
+      const float L = rows_sum(M == -INFINITY ? 0.0f : l[rt] * __builtin_amdgcn_exp2f(m[rt] - M));
+      if (kg == 0) {
+        red[wv][16 * rt + i16][0] = M;
+        red[wv][16 * rt + i16][1] = L;
       }
     }
     __syncthreads();
-    if (tid < R) {
+    for (int r = tid; r < R; r += 256) {
       float M = -INFINITY;
 #pragma unroll
-      for (int w = 0; w < 4; ++w) M = fmaxf(M, red[w][tid][0]);
+      for (int w = 0; w < 4; ++w) M = fmaxf(M, red[w][r][0]);
       float L = 0.0f;
       if (M != -INFINITY) {
 #pragma unroll
         for (int w = 0; w < 4; ++w)
-          if (red[w][tid][0] != -INFINITY) L += red[w][tid][1] * __builtin_amdgcn_exp2f(red[w][tid][0] - M);
+          if (red[w][r][0] != -INFINITY) L += red[w][r][1] * __builtin_amdgcn_exp2f(red[w][r][0] - M);
       }
-      float* out = a.part + (((int64_t)bh * a.P + p) * R + tid) * 2;
+      float* out = a.part + (((int64_t)bh * a.P + p) * R + r) * 2;
       out[0] = M;
       out[1] = L;
     }
@@ -646,8 +676,16 @@ namespace {
 
 struct SnapSizes {
   int64_t part, stats, imp;  // floats
-  int32_t P, R;
+  int32_t P, R, chunk;
 };
+
+// Tokens per workgroup of the score passes: as many as leave about 512 workgroups (two
+// per CU), at most kChunk; a short prompt's few workgroups otherwise run their 64 token
+// steps in turn on an idle GPU.
+int32_t snap_chunk(int64_t bh, int32_t n) {
+  const int64_t even = (((int64_t)n * bh + 511) / 512 + 127) / 128 * 128;
+  return (int32_t)std::max<int64_t>(128, std::min<int64_t>(kChunk, even));
+}
 
 // The selection's slices and scratch for S streams of n positions: slices of at least
 // 4096 positions, as many as keep about 512 workgroups busy.
@@ -699,10 +737,15 @@ void launch_topk(const float* imp, int32_t* keep, int64_t S, int32_t n_tokens, i
 SnapSizes snap_sizes(const kvk_table* t, int32_t n_tokens) {
   const kvk_dims& d = t->d;
   SnapSizes s;
-  s.P = (n_tokens + kChunk - 1) / kChunk;
-  s.R = kWin * (d.n_q_heads / d.n_kv_heads);
   const int64_t bh = (int64_t)d.batch * d.n_kv_heads;
-  s.part = bh * s.P * s.R * 2;
+  s.chunk = snap_chunk(bh, n_tokens);
+  s.P = (n_tokens + s.chunk - 1) / s.chunk;
+  s.R = kWin * (d.n_q_heads / d.n_kv_heads);
+  // Chunk records: at least P, and growing with the prompt (P itself need not), so that
+  // the workspace of a prompt serves every shorter one.
+  const int64_t most = std::max<int64_t>((n_tokens + kChunk - 1) / kChunk,
+                                         std::min<int64_t>((n_tokens + 127) / 128, 512 / bh + 1));
+  s.part = bh * most * s.R * 2;
   s.stats = bh * s.R * 2;
   s.imp = bh * n_tokens;
   return s;
@@ -836,6 +879,7 @@ extern "C" kvk_status kvk_snapkv_select(const kvk_table* t, int32_t layer, const
   a.n = n_tokens;
   a.P = s.P;
   a.R = s.R;
+  a.chunk = s.chunk;
   a.Hkv = d.n_kv_heads;
   a.Hq = d.n_q_heads;
   a.keep_n = d.keep_tokens;
