@@ -343,23 +343,38 @@ struct ProjectedRows {
 // Geometry of the projected write for kept width D: TOK stored tokens per 8-wave
 // workgroup (whole 32-token blocks); the waves split into WC channel groups x WT
 // token groups, wave (wc, wt) owning CTW 16-channel tiles x TTW 16-token tiles of
-// the latent tile.  Each k-step (32 of the model width) stages the W_DKV rows and
-// the hidden-state rows in LDS (NBUF buffers, filled through registers one step
-// ahead); the finished latent tile then takes the LDS as bf16 rows of pitch LP.
+// the latent tile.  Each k-step covers 64 of the model width, whole 128-byte lines of
+// every row it reads, staged through registers into LDS in the order the products
+// read them: two buffers, W_DKV in one at width 1024 (two do not fit).  The finished
+// latent tile then takes the LDS as bf16 rows of pitch LP.
+//
+// What bounds it: the hidden rows from HBM up to d = 128, the products and the LDS
+// traffic that feeds them above.  Measured per layer, 16 x 8192 tokens of width 2048
+// under the profiler (before: 32-wide steps, loads one step ahead that all waves wait
+// for at one place): d = 64 121 us (4.5 TB/s of hidden rows), 128 137, 256 194, 512
+// 277-339 us (1.0 PFLOP/s at the shorter); the four layers 1061 -> 720 us per pass.  d =
+// 1024 from 5120-wide rows, 2 x 8192 tokens: 537 -> 281 us; 1000 tokens at d = 512: 77 ->
+// 64 us; 3 x 300 tokens at d = 128: 45 -> 27 us.
 template <int D>
 struct ProjGeo {
   static constexpr int TOK = D > 512 ? 64 : 128;
   static constexpr int NBLK = TOK / 32;
   static constexpr int CT = D / 16, TT = TOK / 16;
-  static constexpr int WC = CT < 8 ? CT : 8, WT = 8 / WC;
+  static constexpr int WC = D >= 512 ? 8 : (CT < 4 ? CT : 4), WT = 8 / WC;
   static constexpr int CTW = CT / WC, TTW = TT / WT;
-  static constexpr int KP = 32 + 8;                   // staging row pitch (halfs): 16 rows, 16 bank windows
-  static constexpr int NBUF = D > 512 ? 1 : 2;        // width 1024: one 85 KiB buffer
-  static constexpr int NW = (4 * D + 511) / 512;      // 16-byte W_DKV chunks a thread stages per k-step
+  static constexpr int NX = TOK / 64;                 // 16-byte chunks of hidden rows a thread stages per k-step
+  static constexpr int RW = 16 * CTW / WT;            // W_DKV rows a wave stages
+  static constexpr int PH = D > 512 ? 2 : 1;          // phases of a k-step, each with its share of the channels
+  static constexpr int CTP = CTW / PH;
+  static constexpr int NW = RW < 8 ? 1 : RW / 8 / PH;  // chunks of W_DKV a thread stages per phase
+  static constexpr int WB = D > 512 ? 1 : 2;          // W_DKV buffers
+  static constexpr int XBUF = TOK * 64, WBUF = D * 64;  // halfs per staging buffer
   static constexpr int LP = D + 8;                    // latent tile pitch (halfs)
-  static constexpr int STAGE = NBUF * (D + TOK) * KP;
-  static constexpr int LDS_HALFS = STAGE > TOK * LP ? STAGE : TOK * LP;
-  static_assert(CT % WC == 0 && TT % WT == 0 && 4 * TOK <= 512, "tiles must split evenly over the waves");
+  static constexpr int STAGE = 2 * XBUF + WB * WBUF;
+  static constexpr int AMAX = TOK * LP;               // SYMROW maxima (256 bytes) behind the latent tile
+  static constexpr int LDS_HALFS = STAGE > AMAX + 128 ? STAGE : AMAX + 128;
+  static_assert(WB == 1 || NX + NW <= 2 * TTW, "one staging move per group of products");
+  static_assert(CT % WC == 0 && TT % WT == 0 && 16 * CTW % WT == 0, "tiles must split evenly over the waves");
 };
 
 // One 512-thread workgroup per (TOK stored tokens, sequence): the latent tile
@@ -368,89 +383,189 @@ struct ProjGeo {
 // rounded to bf16 into LDS, then the tile's blocks (and the stream's tail block)
 // written by the block writer with all 8 waves.
 template <int D, int BITS, bool KIVI>
-__global__ __launch_bounds__(512) void mla_project_kernel(MlaProjectArgs a) {
+__global__ __launch_bounds__(512, 2) void mla_project_kernel(MlaProjectArgs a) {
   using P = ProjGeo<D>;
   __shared__ __attribute__((aligned(16))) uint16_t lds[P::LDS_HALFS];
-  __shared__ uint32_t amax[2][32];
+  uint32_t(&amax)[2][32] = *reinterpret_cast<uint32_t(*)[2][32]>(lds + P::AMAX);
   const int wg = blockIdx.x, j = blockIdx.y;
   const int b = a.n_seq > 0 ? a.seq_of[j] : j;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, i16 = lane & 15, kg = lane >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, i16 = lane & 15, kg = lane >> 4;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wc = wv % P::WC, wt = wv / P::WC;
   const int row0 = P::TOK * wg;                         // first stored token of the tile
   const int nrow = min(P::TOK, a.n_stored - row0);      // may be <= 0 (the tail slot only)
-  constexpr int BUF = (D + P::TOK) * P::KP;             // halfs per staging buffer: W rows, then hidden rows
-  // W_DKV staging: chunk c = tid + 512 n < 4 D is row c / 4, k 8 (c % 4)
-  const uint16_t* wsrc = a.w + (int64_t)(tid >> 2) * a.H + 8 * (tid & 3);
-  const int64_t wstep = (int64_t)128 * a.H;             // 512 chunks = 128 rows further
-  // hidden-row staging: thread tid < 4 TOK moves row tid / 4, k 8 (tid % 4)
-  const int xr = tid >> 2, xk = 8 * (tid & 3);
-  const bool x_stager = tid < 4 * P::TOK, x_ok = x_stager && xr < nrow;
-  const uint16_t* xsrc = a.x + ((int64_t)b * a.n_tokens +
-                                mla_stored_pos(a.keep, b, a.n_stored, a.n_tokens, x_ok ? row0 + xr : 0)) * a.H + xk;
-  u4v wr[P::NW];
-  auto fetch_w = [&](int k0) {
+  // Rows past the stored ones repeat a valid row; nothing reads their latents.
+  auto x_row = [&](int r) {
+    return a.x + ((int64_t)b * a.n_tokens +
+                  mla_stored_pos(a.keep, b, a.n_stored, a.n_tokens, r < nrow ? row0 + r : 0)) * a.H;
+  };
+  // Staging: 8 consecutive lanes read a whole line of a row.  (W_DKV rows loaded straight
+  // into the products' lane order cost a cache access per 16 bytes: the L1 was busy 79 %
+  // of the time, d = 256 at 16 x 8192 tokens 340 us against 211.)  LDS holds the operands' lane images: (16-row tile, half of
+  // the step) 64 slots of 16 bytes, row r's chunk c at slot 16 (c % 4) + (r % 16 ^ c),
+  // which spreads both the stores and the reads over the banks.
+  const int xc = tid & 7;
+  auto slot_of = [&](int row) { return ((row >> 4) * 2 + (xc >> 2)) * 512 + (16 * (xc & 3) + ((row & 15) ^ xc)) * 8; };
+  const int xr = tid >> 3;  // chunk n: row xr + 64 n
+  const uint16_t* xsrc[P::NX];
 #pragma unroll
-    for (int n = 0; n < P::NW; ++n)
-      if (tid + 512 * n < 4 * D) wr[n] = *reinterpret_cast<const u4v*>(wsrc + n * wstep + k0);
+  for (int n = 0; n < P::NX; ++n) xsrc[n] = x_row(xr + 64 * n) + 8 * xc;
+  const int xdst = slot_of(xr);
+  auto fetch_x = [&](u4v& r, int c, int t) {
+    r = __builtin_nontemporal_load(reinterpret_cast<const u4v*>(xsrc[c] + 64 * t));
   };
-  auto store_w = [&](uint16_t* buf) {
-#pragma unroll
-    for (int n = 0; n < P::NW; ++n)
-      if (tid + 512 * n < 4 * D)
-        *reinterpret_cast<u4v*>(buf + (xr + 128 * n) * P::KP + xk) = wr[n];
+  auto store_x = [&](const u4v& r, int c, int t) {
+    *reinterpret_cast<u4v*>(lds + (t & 1) * P::XBUF + xdst + c * 4096) = r;
   };
-  auto fetch_x = [&](u4v& r, int k0) {
-    r = x_ok ? *reinterpret_cast<const u4v*>(xsrc + k0) : u4v{0u, 0u, 0u, 0u};
+  // W_DKV: wave (wc, wt) moves rows RW wt .. + RW - 1 of channel group wc, 8 per chunk
+  // (fewer than 8: lanes move the same chunk twice)
+  const int wr = P::RW * wt + ((lane >> 3) & (P::RW - 1 < 7 ? P::RW - 1 : 7));
+  const uint32_t woff = (uint32_t)wr * a.H + 8 * xc;
+  const uint16_t* wgroup = a.w + (int64_t)16 * wc * P::CTW * a.H;
+  uint16_t* const wlds = lds + 2 * P::XBUF + wc * P::CTW * 1024;
+  auto fetch_w = [&](u4v& r, int c, int t) {
+    r = *reinterpret_cast<const u4v*>(wgroup + (int64_t)8 * c * a.H + 64 * t + woff);
   };
-  auto store_x = [&](const u4v& r, uint16_t* buf) {
-    if (x_stager) *reinterpret_cast<u4v*>(buf + (D + xr) * P::KP + xk) = r;
+  auto store_w = [&](const u4v& r, int c, int t) {
+    *reinterpret_cast<u4v*>(wlds + (P::WB == 2 ? (t & 1) * P::WBUF : 0) + slot_of(wr + 8 * c)) = r;
   };
   f4 acc[P::CTW][P::TTW];
 #pragma unroll
   for (int j = 0; j < P::CTW; ++j)
 #pragma unroll
     for (int m = 0; m < P::TTW; ++m) acc[j][m] = f4{0.f, 0.f, 0.f, 0.f};
-  // the products of one k-step from a staging buffer
-  auto step = [&](const uint16_t* base) {
+  const int n = nrow > 0 ? a.H / 64 : 0;  // a tile that holds the tail slot alone has no products
+  // Operand tiles of half h of a step: lane (i16, kg) reads row i16, chunk 4 h + kg.
+  auto tile_at = [&](const uint16_t* p, int i, int h) {
+    return *reinterpret_cast<const bf16x8*>(p + i * 1024 + 512 * h + (16 * kg + (i16 ^ (4 * h + kg))) * 8);
+  };
+  // Loads past the last step repeat it (no branch between loads and waits).
+  if constexpr (P::WB == 2) {
+    // Between the products of a step, chunk by chunk, the next step's rows go from the
+    // registers to the other LDS buffers (last read before the previous barrier) and
+    // the loads of the step after it take their place: every load has a whole step to
+    // arrive, and LDS stores, loads and products overlap instead of taking turns.
+    u4v xq[P::NX], wq[P::NW];
+    auto step = [&](int t) {
+      const uint16_t* xbase = lds + (t & 1) * P::XBUF + wt * P::TTW * 1024;
+      const uint16_t* wbase = wlds + (t & 1) * P::WBUF;
+      const int tn = min(t + 2, n - 1);
+      constexpr int G = 2 * P::TTW;
+      bf16x8 wa[2][P::CTW], xb[3];
+#pragma unroll
+      for (int j = 0; j < P::CTW; ++j) wa[0][j] = tile_at(wbase, j, 0);
+      xb[0] = tile_at(xbase, 0, 0);
+      xb[1] = tile_at(xbase, 1, 0);
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        const int h = g / P::TTW, m = g % P::TTW;
+        if (g + 2 < G) xb[(g + 2) % 3] = tile_at(xbase, (g + 2) % P::TTW, (g + 2) / P::TTW);
+        if (g == P::TTW / 2) {
+#pragma unroll
+          for (int j = 0; j < P::CTW; ++j) wa[1][j] = tile_at(wbase, j, 1);
+        }
+        if (g < P::NX) {
+          store_x(xq[g], g, t + 1);
+          fetch_x(xq[g], g, tn);
+        } else if (g - P::NX < P::NW) {
+          store_w(wq[g - P::NX], g - P::NX, t + 1);
+          fetch_w(wq[g - P::NX], g - P::NX, tn);
+        }
+#pragma unroll
+        for (int j = 0; j < P::CTW; ++j) acc[j][m] = mfmab(wa[h][j], xb[g % 3], acc[j][m]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      __syncthreads();
+    };
+    auto fetch = [&](int t) {
+#pragma unroll
+      for (int c = 0; c < P::NX; ++c) fetch_x(xq[c], c, t);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int c = 0; c < P::NW; ++c) fetch_w(wq[c], c, t);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    if (n > 0) {
+      fetch(0);
+#pragma unroll
+      for (int c = 0; c < P::NX; ++c) store_x(xq[c], c, 0);
+#pragma unroll
+      for (int c = 0; c < P::NW; ++c) store_w(wq[c], c, 0);
+      fetch(min(1, n - 1));
+      __syncthreads();
+      for (int t = 0; t < n; ++t) step(t);
+    }
+  } else {
+    // W_DKV in one LDS buffer (two do not fit): each wave refills its own rows a phase at a
+    // time, after its reads of them (a wave's LDS operations stay in order).  W_DKV is
+    // loaded before the hidden rows: loads return in order, so the wait for the former
+    // leaves the latter in flight.
+    u4v xring[2][P::NX];  // xring[t % 2] holds step t's hidden rows until they enter LDS
+    u4v wq[P::NW];
+    auto step = [&](int t, u4v (&cur)[P::NX], const u4v (&nxt)[P::NX]) {
+      const uint16_t* xbase = lds + (t & 1) * P::XBUF + wt * P::TTW * 1024;
+#pragma unroll
+      for (int ph = 0; ph < P::PH; ++ph) {
+#pragma unroll
+        for (int c = 0; c < P::NW; ++c) fetch_w(wq[c], ph * P::NW + c, min(t + 1, n - 1));
+        if (ph == P::PH - 1) {
+#pragma unroll
+          for (int c = 0; c < P::NX; ++c) fetch_x(cur[c], c, min(t + 2, n - 1));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          bf16x8 wa[P::CTP];
+#pragma unroll
+          for (int j = 0; j < P::CTP; ++j) wa[j] = tile_at(wlds, ph * P::CTP + j, h);
+#pragma unroll
+          for (int m = 0; m < P::TTW; ++m) {
+            const bf16x8 xb = tile_at(xbase, m, h);
+#pragma unroll
+            for (int j = 0; j < P::CTP; ++j)
+              acc[ph * P::CTP + j][m] = mfmab(wa[j], xb, acc[ph * P::CTP + j][m]);
+          }
+        }
+#pragma unroll
+        for (int c = 0; c < P::NW; ++c) store_w(wq[c], ph * P::NW + c, t + 1);
+      }
+#pragma unroll
+      for (int c = 0; c < P::NX; ++c) store_x(nxt[c], c, t + 1);
+      __syncthreads();
+    };
+    if (n > 0) {
+#pragma unroll
+      for (int c = 0; c < P::NX; ++c) fetch_x(xring[0][c], c, 0);
+#pragma unroll
+      for (int c = 0; c < P::NX; ++c) fetch_x(xring[1][c], c, min(1, n - 1));
+#pragma unroll
+      for (int ph = 0; ph < P::PH; ++ph) {
+#pragma unroll
+        for (int c = 0; c < P::NW; ++c) fetch_w(wq[c], ph * P::NW + c, 0);
+#pragma unroll
+        for (int c = 0; c < P::NW; ++c) store_w(wq[c], ph * P::NW + c, 0);
+      }
+#pragma unroll
+      for (int c = 0; c < P::NX; ++c) store_x(xring[0][c], c, 0);
+      __syncthreads();
+      int t = 0;
+      for (; t + 2 <= n; t += 2) {
+        step(t, xring[0], xring[1]);
+        step(t + 1, xring[1], xring[0]);
+      }
+      if (t < n) step(t, xring[0], xring[1]);
+    }
+  }
+  if ((a.H & 32) && nrow > 0) {  // a model width that is an odd multiple of 32: the last half step, straight from memory
     bf16x8 xb[P::TTW];
 #pragma unroll
     for (int m = 0; m < P::TTW; ++m)
-      xb[m] = *reinterpret_cast<const bf16x8*>(base + (D + 16 * (wt * P::TTW + m) + i16) * P::KP + 8 * kg);
+      xb[m] = *reinterpret_cast<const bf16x8*>(x_row(16 * (wt * P::TTW + m) + i16) + 64 * n + 8 * kg);
 #pragma unroll
     for (int j = 0; j < P::CTW; ++j) {
-      const bf16x8 wa = *reinterpret_cast<const bf16x8*>(base + (16 * (wc * P::CTW + j) + i16) * P::KP + 8 * kg);
+      const bf16x8 wa = *reinterpret_cast<const bf16x8*>(wgroup + ((int64_t)16 * j + i16) * a.H + 64 * n + 8 * kg);
 #pragma unroll
       for (int m = 0; m < P::TTW; ++m) acc[j][m] = mfmab(wa, xb[m], acc[j][m]);
-    }
-  };
-  const int nks = a.H / 32;
-  u4v xr0;
-  fetch_w(0);
-  fetch_x(xr0, 0);
-  store_w(lds);
-  store_x(xr0, lds);
-  __syncthreads();
-  for (int ks = 0; ks < nks; ++ks) {
-    const int buf = P::NBUF == 2 ? (ks & 1) : 0;
-    const bool more = ks + 1 < nks;  // uniform
-    if (more) {
-      fetch_w(32 * (ks + 1));
-      fetch_x(xr0, 32 * (ks + 1));
-    }
-    step(lds + buf * BUF);
-    if constexpr (P::NBUF == 2) {
-      if (more) {  // the other buffer was last read before the previous barrier
-        store_w(lds + (buf ^ 1) * BUF);
-        store_x(xr0, lds + (buf ^ 1) * BUF);
-      }
-      __syncthreads();
-    } else {
-      __syncthreads();  // every wave is done with the buffer
-      if (more) {
-        store_w(lds);
-        store_x(xr0, lds);
-        __syncthreads();
-      }
     }
   }
   // the latent tile, bf16, over the staging buffers (all reads of them are done)

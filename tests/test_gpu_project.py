@@ -93,6 +93,17 @@ def test_project_other_widths(r, d):
     _run(256, d, 4, kvk.KIVI32, 70, seed=200 + d, r=r)
 
 
+@pytest.mark.parametrize("H,d,r,n", [(32, 64, 512, 70), (96, 512, 512, 128), (160, 128, 512, 257),
+                                     (64, 256, 512, 129), (224, 1024, 1024, 200), (128, 1024, 1024, 64)])
+@pytest.mark.parametrize("qs", [kvk.KIVI32, kvk.SYMROW], ids=["kivi32", "symrow"])
+def test_project_model_widths(qs, H, d, r, n):
+    """The edges of the 64-wide k-steps and of the token tiles: fewer steps than the
+    loads run ahead, odd multiples of 32 (a half step), whole tiles (a tail slot
+    alone in its tile) and one token past a tile."""
+    say(f"case project H={H} r={r} d={d} n={n} qs={qs}")
+    _run(H, d, 8, qs, n, seed=600 + H + d, r=r, decode=False)
+
+
 @pytest.mark.parametrize("keep", [150, 128])
 def test_project_eviction(keep):
     """Stored tokens are a sorted subset of 300 (150: a ragged tail; 128: whole
