@@ -48,6 +48,7 @@ constexpr int kW = 256, kHeads = 4, kDh = 64, kFfn = 1024, kMaxActions = 32;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kRmsEps = 1e-6f;
 constexpr double kRopeBase = 10000.0;
+constexpr int kPoolRows = 64;  // rows per partial sum of the time average
 constexpr int kRec = kDh + 4;  // key-split record: 64 outputs, max, sum, 2 pad (16-byte rows)
 
 __device__ __forceinline__ f4 mfma_bf(bf16x8 a, bf16x8 b, f4 c) {
@@ -255,7 +256,12 @@ __global__ __launch_bounds__(256) void sel_rmsnorm_kernel(const float* x, const 
 // max exceeds it by more than 8, so probabilities stay below 2^8 (exact in the
 // normalised result; fp32 sums) and the rescaling of the accumulators is rare.  Only
 // the last key tile is masked.
-__global__ __launch_bounds__(256) void sel_attention_kernel(const uint16_t* qk, const uint16_t* vt, int vt_pitch,
+//
+// The exponentials and the products take turns within a wave (a tile's chain is
+// scores, maximum, probabilities, product), so it is the waves of a SIMD that overlap
+// them: three (168 registers) instead of two (8192 tokens: 112 -> 107 us with the keys
+// in three splits instead of two).
+__global__ __launch_bounds__(256, 3) void sel_attention_kernel(const uint16_t* qk, const uint16_t* vt, int vt_pitch,
                                                             uint16_t* out, int T, int key_len, float* part) {
   constexpr int KT = 64;
   __shared__ uint16_t ks[2][KT][kDh + 8];  // key rows of the tile
@@ -455,14 +461,16 @@ __global__ __launch_bounds__(256) void sel_attn_merge_kernel(const float* part, 
   *reinterpret_cast<uint2*>(out + q * kW + h * kDh + 4 * c4) = w2;
 }
 
-// Partial column sums of the RMS-normalised rows over chunks of 256 rows:
+// Partial column sums of the RMS-normalised rows over chunks of kPoolRows rows (a
+// chunk per workgroup; 256-row chunks left a prompt of 8192 tokens on 32 of the 256
+// CUs: 34 us, now 10):
 // part[chunk][c] = sum_t x[t][c] / rms(x[t]) (the final gain is applied to the
 // mean).  Wave rg takes every fourth row of the chunk, lane c4 columns 4 c4 .. + 3;
 // the four waves meet in LDS.
 __global__ __launch_bounds__(256) void sel_pool_kernel(const float* x, float* part, int T) {
   __shared__ float red[4][kW];
   const int tid = threadIdx.x, c4 = tid & 63, rg = tid >> 6, chunk = blockIdx.x;
-  const int t0 = chunk * 256, t1 = min(T, t0 + 256);
+  const int t0 = chunk * kPoolRows, t1 = min(T, t0 + kPoolRows);
   f4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 4
   for (int t = t0 + rg; t < t1; t += 4) {
@@ -485,13 +493,17 @@ __global__ __launch_bounds__(256) void sel_heads_kernel(const float* part, int n
                                                         float* logits, int32_t* action) {
   __shared__ float red[4][kMaxActions];
   const int c = threadIdx.x, lane = c & 63, wv = c >> 6, l = blockIdx.x;
-  float f4s[4] = {0.0f, 0.0f, 0.0f, 0.0f};  // four independent chains over the chunks
+  float sums[16] = {};  // sixteen independent chains over the chunks, their loads in flight together
   int k = 0;
-  for (; k + 4 <= n_chunks; k += 4)
+  for (; k + 16 <= n_chunks; k += 16)
 #pragma unroll
-    for (int u = 0; u < 4; ++u) f4s[u] += part[(int64_t)(k + u) * kW + c];
-  for (; k < n_chunks; ++k) f4s[0] += part[(int64_t)k * kW + c];
-  float f = (f4s[0] + f4s[1] + f4s[2] + f4s[3]) / (float)T * bf16_to_f32(g_final[c]);
+    for (int u = 0; u < 16; ++u) sums[u] += part[(int64_t)(k + u) * kW + c];
+  for (; k < n_chunks; ++k) sums[0] += part[(int64_t)k * kW + c];
+#pragma unroll
+  for (int o = 8; o >= 1; o >>= 1)
+#pragma unroll
+    for (int u = 0; u < o; ++u) sums[u] += sums[u + o];
+  float f = sums[0] / (float)T * bf16_to_f32(g_final[c]);
   if (film) f = fmaf(f, film[c], f) + film[kW + c];
   for (int a = 0; a < n_actions; ++a) {
     const float z = wave_sum(f * bf16_to_f32(w_head[((int64_t)l * n_actions + a) * kW + c]));
@@ -535,16 +547,34 @@ SelOffsets sel_offsets(int d_model, int L, int A) {
 }
 
 struct SelWorkspace {
-  int64_t x, h, qk, vt, f1, rope, part, splitk, attn, total;  // byte offsets
+  int64_t x, h, qk, vt, rope, f1, splitk, total;  // byte offsets
   int vt_pitch;
 };
 
-// Key splits of the attention when its 128-query workgroups alone would be fewer
-// than about 512: each split at least 256 keys, a multiple of 64; no empty split.
-// Returns the split count; *key_len gets the keys per split.
-int sel_attn_splits(int T, int* key_len) {
+// Bytes of the attention's key-split records that the workspace holds behind f1 and
+// the split-K sums, which are free while the attention runs.
+int64_t sel_attn_reserve(int T) {
   const int wgs = (T + 127) / 128 * kHeads;
   const int sp = std::min((512 + wgs - 1) / wgs, T / 256);
+  if (sp <= 1) return 0;
+  const int key_len = ((T + sp - 1) / sp + 63) / 64 * 64;
+  return (int64_t)((T + key_len - 1) / key_len) * T * kHeads * kRec * 4;
+}
+
+// Key splits of the attention: as many as make the 128-query workgroups' rounds over
+// the 768 places (three per CU) the shortest, each split at least 256 keys, a multiple
+// of 64, their records within `room` bytes; no empty split.  A further split has to
+// save 5 % of the time, for its records and their merge.  Returns the split count;
+// *key_len gets the keys per split.
+int sel_attn_splits(int T, int64_t room, int* key_len) {
+  const int wgs = (T + 127) / 128 * kHeads;
+  const int cap = (int)std::min<int64_t>(std::min(T / 256, 16), room / ((int64_t)T * kHeads * kRec * 4));
+  int sp = 1;
+  double best = (wgs + 767) / 768;
+  for (int s = 2; s <= cap; ++s) {
+    const double t = (double)((wgs * s + 767) / 768) / s;
+    if (t < 0.95 * best) best = t, sp = s;
+  }
   if (sp <= 1) {
     *key_len = T;
     return 1;
@@ -574,15 +604,14 @@ SelWorkspace sel_workspace(int T) {
   w.h = kvk::round256(w.x + (int64_t)Tp * kW * 4);           // bf16 [T][256] normalised / attention output
   w.qk = kvk::round256(w.h + (int64_t)Tp * kW * 2);          // bf16 [T][512] rotated q | k
   w.vt = kvk::round256(w.qk + (int64_t)Tp * 2 * kW * 2);     // bf16 [256][Tp]
-  w.f1 = kvk::round256(w.vt + (int64_t)kW * Tp * 2);         // bf16 [T][1024] SiLU(gate) * up
-  w.rope = kvk::round256(w.f1 + (int64_t)Tp * kFfn * 2);     // fp32 [T][32] (cos, sin)
-  w.part = kvk::round256(w.rope + (int64_t)Tp * (kDh / 2) * 8);  // fp32 [chunks][256]
-  w.splitk = kvk::round256(w.part + (int64_t)((T + 255) / 256) * kW * 4);  // fp32 [splits][T][256]
+  w.rope = kvk::round256(w.vt + (int64_t)kW * Tp * 2);       // fp32 [T][32] (cos, sin)
+  // f1, the split-K sums and the room behind them also hold the attention's key-split
+  // records fp32 [splits][T][4][kRec], and f1 the time average's partial sums fp32 [chunks][256]
+  w.f1 = kvk::round256(w.rope + (int64_t)Tp * (kDh / 2) * 8);  // bf16 [T][1024] SiLU(gate) * up
+  w.splitk = kvk::round256(w.f1 + (int64_t)Tp * kFfn * 2);   // fp32 [splits][T][256]
   const int max_splits = std::min(kSplitMax, (512 + (T + 63) / 64 - 1) / ((T + 63) / 64));
-  w.attn = kvk::round256(w.splitk + (max_splits > 1 ? (int64_t)max_splits * T * kW * 4 : 0));  // fp32 [splits][T][4][kRec]
-  int key_len = 0;
-  const int attn_splits = sel_attn_splits(T, &key_len);
-  w.total = kvk::round256(w.attn + (attn_splits > 1 ? (int64_t)attn_splits * T * kHeads * kRec * 4 : 0));
+  w.total = kvk::round256(kvk::round256(w.splitk + (max_splits > 1 ? (int64_t)max_splits * T * kW * 4 : 0)) +
+                          sel_attn_reserve(T));
   return w;
 }
 
@@ -635,7 +664,7 @@ extern "C" kvk_status kvk_selector_forward(int32_t d_model, int32_t n_layers, in
   uint16_t* vt = reinterpret_cast<uint16_t*>(ws + Wk.vt);
   uint16_t* f1 = reinterpret_cast<uint16_t*>(ws + Wk.f1);
   float2* rope = reinterpret_cast<float2*>(ws + Wk.rope);
-  float* part = reinterpret_cast<float*>(ws + Wk.part);
+  float* part = reinterpret_cast<float*>(ws + Wk.f1);
   const int T = n_tokens;
   auto gemm = [&](int epi, const uint16_t* a, int64_t w_off, int N, int K) {
     GemmArgs g;
@@ -679,8 +708,8 @@ extern "C" kvk_status kvk_selector_forward(int32_t d_model, int32_t n_layers, in
     gemm(kQkv, hbuf, w_qkv, 3 * kW, kW);
     {
       int key_len = 0;
-      const int sp = sel_attn_splits(T, &key_len);
-      float* apart = sp > 1 ? reinterpret_cast<float*>(ws + Wk.attn) : nullptr;
+      const int sp = sel_attn_splits(T, Wk.total - Wk.f1, &key_len);
+      float* apart = sp > 1 ? reinterpret_cast<float*>(ws + Wk.f1) : nullptr;
       hipLaunchKernelGGL(sel_attention_kernel, dim3((unsigned)((T + 127) / 128), kHeads, (unsigned)sp), b256, 0,
                          stream, qk, vt, Wk.vt_pitch, hbuf, T, key_len, apart);
       if (sp > 1)
@@ -692,7 +721,7 @@ extern "C" kvk_status kvk_selector_forward(int32_t d_model, int32_t n_layers, in
     gemm(kSwiGlu, hbuf, w_gu, 2 * kFfn, kW);
     gemm(kAddF32, f1, w_down, kW, kFfn);
   }
-  const int chunks = (T + 255) / 256;
+  const int chunks = (T + kPoolRows - 1) / kPoolRows;
   hipLaunchKernelGGL(sel_pool_kernel, dim3((unsigned)chunks), b256, 0, stream, x, part, T);
   hipLaunchKernelGGL(sel_heads_kernel, dim3((unsigned)n_layers), b256, 0, stream, part, chunks, T, wp + O.g_final,
                      film, wp + O.w_head, wp + O.b_head, n_actions, depth, logits, actions);

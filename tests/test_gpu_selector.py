@@ -113,6 +113,13 @@ def test_selector_matches_oracle(T, L, A, depth, film):
     _compare(got, act, ref, depth)
 
 
+@pytest.mark.parametrize("T", [64, 65, 1025, 2112])
+def test_selector_chunk_edges(T):
+    """The edges of the time average's 64-row chunks and of its sixteen chains (1, 2, 17
+    and 33 chunks), and of the attention's key splits (none, 4 and 8, the last one short)."""
+    test_selector_matches_oracle(T, 7, 5, True, False)
+
+
 def test_selector_positions_matter():
     """Reversing the prompt changes the kernel's logits by far more than the tolerance,
     as it changes the oracle's (rotary positions; a model without them is invariant)."""
