@@ -130,41 +130,23 @@ struct Rows<true> {
   __device__ __forceinline__ void renew() {}
 };
 
-// min and max of eight values as v_min3 / v_max3 trees.  The instructions are written
-// out: from fminf the compiler first quiets every operand (a v_max of its own per
-// loaded value).  A NaN operand is skipped, as by fminf.
-__device__ __forceinline__ float min3(float a, float b, float c) {
-  float r;
-  asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
-}
-__device__ __forceinline__ float max3(float a, float b, float c) {
-  float r;
-  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
-}
-__device__ __forceinline__ float min2(float a, float b) {
-  float r;
-  asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-  return r;
-}
-__device__ __forceinline__ float max2(float a, float b) {
-  float r;
-  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-  return r;
-}
+// Minima and maxima, which the compiler forms as v_min3 / v_max3 trees.  A quiet NaN
+// operand is skipped (a signalling one, which no arithmetic gives, can hide the operands
+// before it).  Written as fminf / fmaxf and not as the instructions in asm: the results
+// meet lane swaps and DPP reads, which need two wait states after a vector write, and the
+// compiler counts those only for instructions that it sees.
 template <class F>
 __device__ __forceinline__ float min8(F x) {
-  return min2(min3(min3(x(0), x(1), x(2)), x(3), x(4)), min3(x(5), x(6), x(7)));
+  return fminf(fminf(fminf(fminf(fminf(x(0), x(1)), x(2)), x(3)), x(4)), fminf(fminf(x(5), x(6)), x(7)));
 }
 template <class F>
 __device__ __forceinline__ float max8v(F x) {
-  return max2(max3(max3(x(0), x(1), x(2)), x(3), x(4)), max3(x(5), x(6), x(7)));
+  return fmaxf(fmaxf(fmaxf(fmaxf(fmaxf(x(0), x(1)), x(2)), x(3)), x(4)), fmaxf(fmaxf(x(5), x(6)), x(7)));
 }
-// |x| of eight values.
+// Largest |x| of eight values, 0 where all are NaN.
 template <class F>
 __device__ __forceinline__ float amax8(F x) {
-  return max8v([&](int i) { return fabsf(x(i)); });
+  return fmaxf(max8v([&](int i) { return fabsf(x(i)); }), 0.0f);
 }
 
 // ---------------------------------------------------------------------------
@@ -299,14 +281,14 @@ __device__ __forceinline__ int v_chunk_byte(int c, int tg) {
 // Reduction over the token sets of one channel's minimum or maximum, all lanes ending
 // with it (d_h 64: the sets are 8 and 16 lanes apart).
 __device__ __forceinline__ float sets_min64(float x) {
-  x = min2(x, dpp<0x128>(x));  // row_ror:8
+  x = fminf(x, dpp<0x128>(x));  // row_ror:8
   const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return min2(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  return fminf(__uint_as_float(a[0]), __uint_as_float(a[1]));
 }
 __device__ __forceinline__ float sets_max64(float x) {
-  x = max2(x, dpp<0x128>(x));
+  x = fmaxf(x, dpp<0x128>(x));
   const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return max2(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  return fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
 }
 
 struct Pair {
@@ -349,13 +331,13 @@ __device__ __forceinline__ void kivi_key_groups(const R& rows, int q, int tg, ui
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const Pair a = swap16(mn[k], mn[k + 4]), b = swap16(mx[k], mx[k + 4]);
-      rn[k] = min2(a.a, a.b);
-      rx[k] = max2(b.a, b.b);
+      rn[k] = fminf(a.a, a.b);
+      rx[k] = fmaxf(b.a, b.b);
     }
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
       const Pair a = swap32(rn[k], rn[k + 2]), b = swap32(rx[k], rx[k + 2]);
-      const Group g = make_group<BITS>(min2(a.a, a.b), max2(b.a, b.b));
+      const Group g = make_group<BITS>(fminf(a.a, a.b), fmaxf(b.a, b.b));
       const int c = 8 * q + k + 2 * (tg >> 1) + 4 * (tg & 1);
       kmeta[c] = (uint16_t)g.sz;
       kmeta[D + c] = (uint16_t)(g.sz >> 16);
@@ -404,13 +386,13 @@ __device__ __forceinline__ void token_groups(const R& rows, int q, float (&s)[8]
     float an[4], ax[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      an[k] = min2(o1 ? mn[2 * k + 1] : mn[2 * k], dpp<kQuadXor1>(o1 ? mn[2 * k] : mn[2 * k + 1]));
-      ax[k] = max2(o1 ? mx[2 * k + 1] : mx[2 * k], dpp<kQuadXor1>(o1 ? mx[2 * k] : mx[2 * k + 1]));
+      an[k] = fminf(o1 ? mn[2 * k + 1] : mn[2 * k], dpp<kQuadXor1>(o1 ? mn[2 * k] : mn[2 * k + 1]));
+      ax[k] = fmaxf(o1 ? mx[2 * k + 1] : mx[2 * k], dpp<kQuadXor1>(o1 ? mx[2 * k] : mx[2 * k + 1]));
     }
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
-      const float bn = min2(o2 ? an[k + 2] : an[k], dpp<kQuadXor2>(o2 ? an[k] : an[k + 2]));
-      const float bx = max2(o2 ? ax[k + 2] : ax[k], dpp<kQuadXor2>(o2 ? ax[k] : ax[k + 2]));
+      const float bn = fminf(o2 ? an[k + 2] : an[k], dpp<kQuadXor2>(o2 ? an[k] : an[k + 2]));
+      const float bx = fmaxf(o2 ? ax[k + 2] : ax[k], dpp<kQuadXor2>(o2 ? ax[k] : ax[k + 2]));
       const Group g = make_group<BITS>(bn, bx);
       const float szf = __uint_as_float(g.sz);
 #define KVK_FROM_QUAD(E, CTRL) \
@@ -428,12 +410,12 @@ __device__ __forceinline__ void token_groups(const R& rows, int q, float (&s)[8]
 #pragma unroll
     for (int n = 0; n < 8; ++n) {
       float a = mn[n], b = mx[n];
-      a = min2(a, dpp<kQuadXor1>(a));
-      b = max2(b, dpp<kQuadXor1>(b));
-      a = min2(a, dpp<kQuadXor2>(a));
-      b = max2(b, dpp<kQuadXor2>(b));
-      a = min2(a, dpp<kHalfRowMirror>(a));
-      b = max2(b, dpp<kHalfRowMirror>(b));
+      a = fminf(a, dpp<kQuadXor1>(a));
+      b = fmaxf(b, dpp<kQuadXor1>(b));
+      a = fminf(a, dpp<kQuadXor2>(a));
+      b = fmaxf(b, dpp<kQuadXor2>(b));
+      a = fminf(a, dpp<kHalfRowMirror>(a));
+      b = fmaxf(b, dpp<kHalfRowMirror>(b));
       const Group g = make_group<BITS>(a, b);
       s[n] = g.s;
       y[n] = g.y;

@@ -10,7 +10,7 @@ import torch
 from oracle import cache as OC
 from paper_2609_37988_amd import kvk, synth
 
-from gpu_common import TOL, Case, meaningful, oracle_rows, oracle_stream, rel_err, say
+from gpu_common import DEV, TOL, Case, meaningful, oracle_rows, oracle_stream, rel_err, say
 
 pytestmark = pytest.mark.gpu
 
@@ -152,6 +152,65 @@ def test_eviction_gather(bits):
     out = _np(c.decode(q.cuda(), keep, 0.09))
     ref = _oracle_out(c, {0: (_np(k), _np(v))}, q, keep, 0.09, {0: kidx})
     assert rel_err(out, ref) <= TOL
+
+
+@pytest.mark.parametrize("bits", [8, 4, 2])
+@pytest.mark.parametrize("D,dtype", [(128, torch.bfloat16), (64, torch.bfloat16), (128, torch.float32)])
+@pytest.mark.parametrize("qs", [kvk.KIVI32, kvk.SYMROW, kvk.GROUP64], ids=["kivi32", "symrow", "group64"])
+def test_nan_values(qs, D, dtype, bits):
+    """A NaN takes no part in its group's minimum, maximum or row maximum and gets the
+    lowest code; a SYMROW row of NaNs alone stores a zero scale.  Prefill write and group flush alike."""
+    say(f"case nan qs={qs} D={D} {dtype} bits={bits}")
+    B, H, n = 1, 4, 64
+    gen = torch.Generator().manual_seed(1200 + bits)
+    k, v = synth.kv_random(1201 + bits, B, H, n, D, dtype=dtype)
+    at = [torch.rand(x.shape, generator=gen) < 0.2 for x in (k, v)]
+    at[0][:, :, 0::2] = False  # a clean neighbour, for the stand-in: the next token's value (KIVI32 keys),
+    at[1][..., 1::2] = False   # or the next channel's
+    clean = [k.clone(), v.clone()]
+    if qs == kvk.KIVI32:
+        clean[0][:, :, 1::2] = torch.where(at[0][:, :, 1::2], k[:, :, 0::2], k[:, :, 1::2])
+    else:
+        at[0][:] = False
+        at[0][..., 0::2] = torch.rand((B, H, n, D // 2), generator=gen) < 0.4
+        clean[0][..., 0::2] = torch.where(at[0][..., 0::2], k[..., 1::2], k[..., 0::2])
+    clean[1][..., 0::2] = torch.where(at[1][..., 0::2], v[..., 1::2], v[..., 0::2])
+    for x, m in zip((k, v), at):
+        x[m] = float("nan")
+    if qs == kvk.SYMROW:  # rows of NaNs alone
+        for x, c, m in zip((k, v), clean, at):
+            x[:, 1, 5::8] = float("nan")
+            c[:, 1, 5::8] = 0
+            m[:, 1, 5::8] = True
+
+    def written(kk, vv):
+        c = Case(1, 4 * H, H, D, B, n, [(0, bits)], qscheme=qs)
+        c.compress(0, kk.to(DEV), vv.to(DEV), n)
+        return c, c.dequant(0, n)
+
+    c, got = written(k, v)
+    _, ref = written(*clean)
+    levels = 2 ** (bits - 1) - 1
+    for x, g, r, m, keys in zip(clean, got, ref, at, (True, False)):
+        x, g, r = x.float(), g.cpu(), r.cpu()
+        if qs == kvk.KIVI32 and keys:
+            low = x.reshape(B, H, n // 32, 32, D).amin(3, keepdim=True).expand(-1, -1, -1, 32, -1).reshape(x.shape)
+        elif qs == kvk.SYMROW:  # code -q of the stored bf16 scale
+            low = -levels * (x.abs().amax(-1, keepdim=True) / levels).bfloat16().float().expand(x.shape)
+        else:
+            w = 32 if qs == kvk.KIVI32 else 64
+            low = x.reshape(B, H, n, D // w, w).amin(-1, keepdim=True).expand(-1, -1, -1, -1, w).reshape(x.shape)
+        if qs != kvk.SYMROW:
+            low = low.half().float()
+        assert torch.equal(g, torch.where(m, low, r))
+    # the same tokens with the last one appended: the flush forms the same block
+    if dtype == torch.bfloat16:
+        f = Case(1, 4 * H, H, D, B, n, [(0, bits)], qscheme=qs)
+        f.compress(0, k[:, :, :n - 1].to(DEV), v[:, :, :n - 1].to(DEV), n - 1)
+        kvk.append_token(f.table, 0, 1, k[None, :, :, n - 1].contiguous().to(DEV),
+                         v[None, :, :, n - 1].contiguous().to(DEV), n - 1, f.arena)
+        for x, y in zip(got, f.dequant(0, n)):
+            assert torch.equal(x, y)
 
 
 @pytest.mark.parametrize("n", [1, 31, 32, 33, 64])
