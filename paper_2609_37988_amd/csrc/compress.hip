@@ -21,6 +21,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "kvk_device.h"
@@ -91,14 +92,21 @@ __device__ __forceinline__ u4v pack_bf16(f4 lo, f4 hi) {
   return r;
 }
 
-// A lane's eight rows of eight channels, as loaded: bf16 packed, or fp32.
+// A lane's eight rows of eight channels, as loaded: bf16 packed, or fp32.  NT: loaded
+// non-temporally.  Not fp32 rows: a row's lanes read it with two loads, each half of
+// every line, and the second then misses (d_h 128, 4 x 8 KV heads x 8192 tokens, int8:
+// 72 -> 55 us with plain loads, 76 -> 64 with inputs that rotate over 1 GiB; d_h 64, 39
+// -> 30 and 43 -> 34).
 template <bool F32>
 struct Rows;
 template <>
 struct Rows<false> {
   u4v w[8];
+  template <bool NT>
   __device__ __forceinline__ void load(const void* base, int64_t e, int n) {
-    w[n] = __builtin_nontemporal_load(reinterpret_cast<const u4v*>(static_cast<const uint16_t*>(base) + e));
+    const u4v* p = reinterpret_cast<const u4v*>(static_cast<const uint16_t*>(base) + e);
+    if constexpr (NT) w[n] = __builtin_nontemporal_load(p);
+    else w[n] = *p;
   }
   __device__ __forceinline__ float get(int n, int c) const {
     const uint32_t x = w[n][c >> 1];
@@ -120,10 +128,11 @@ struct Rows<false> {
 template <>
 struct Rows<true> {
   f4 lo[8], hi[8];
+  template <bool NT>
   __device__ __forceinline__ void load(const void* base, int64_t e, int n) {
     const f4* p = reinterpret_cast<const f4*>(static_cast<const float*>(base) + e);
-    lo[n] = __builtin_nontemporal_load(p);
-    hi[n] = __builtin_nontemporal_load(p + 1);
+    lo[n] = p[0];
+    hi[n] = p[1];
   }
   __device__ __forceinline__ float get(int n, int c) const { return c < 4 ? lo[n][c] : hi[n][c - 4]; }
   __device__ __forceinline__ u4v bf16(int n) const { return pack_bf16(lo[n], hi[n]); }
@@ -604,22 +613,34 @@ __device__ __forceinline__ void row_elements(const CompressArgs& a, int in_strea
   for (int n = 0; n < 8; ++n) e[n] = ((int64_t)in_stream * a.n_tokens + pos[n]) * D + 8 * q;
 }
 
+// Waves of a workgroup.  One at d_h 64 for fp32 inputs and for copies, whose launches are
+// short and last as long as their fullest CU (4 x 8 KV heads x 8192 tokens, fp32 inputs,
+// int8: 36.3 -> 33.9 us; bf16 copy 27.3 -> 26.3; but quantised bf16 inputs 22.3 -> 23.2).
+template <int D, int BITS, bool F32>
+constexpr int kWriteWaves = D == 64 && (F32 || BITS == 16) ? 1 : 4;
+
 // One wave writes one 32-token block of one stream (two at d_h 64), with BITS-bit codes
 // (or bf16 at BITS = 16; a stream's tail block is always bf16).  The keys' and values'
 // loads are all issued first for bf16 inputs (16 KiB in flight per wave).
 //
 // Bound: HBM and the vector units about equally (d_h 128, KIVI32: about 14 vector
 // operations per value; the input is read and the codes are written once).
+//
+// Loads are non-temporal where bf16 rows are quantised (14B mixed stack, 32 anchors: 1264
+// -> 1170 us), not where they are copied: inputs still in the last-level cache take 41.5 us
+// at d_h 128 (4 x 8 KV heads x 8192 tokens) against 45.7, others 49.3 against 47.7.
 template <int D, int BITS, int QS, bool F32>
-__global__ __launch_bounds__(256, F32 ? 3 : 4) void compress_kernel(CompressArgs a) {
+__global__ __launch_bounds__((64 * kWriteWaves<D, BITS, F32>), F32 ? 3 : 4) void compress_kernel(CompressArgs a) {
   using L = Lanes<D>;
+  constexpr int kWaves = kWriteWaves<D, BITS, F32>;
+  constexpr bool kNt = !F32 && BITS != 16;
   constexpr int kImg = image_bytes<D, BITS, QS>();
-  __shared__ __align__(16) uint8_t img_all[4 * L::kBlocks * kImg];
+  __shared__ __align__(16) uint8_t img_all[kWaves * L::kBlocks * kImg];
 
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l = lane % L::kPerBlock, q = l % L::kQ, tg = l / L::kQ, sub = lane / L::kPerBlock;
   const int nblk = a.nbf + 1;
-  const uint32_t id = (blockIdx.x * 4 + wave) * L::kBlocks + sub;
+  const uint32_t id = (blockIdx.x * kWaves + wave) * L::kBlocks + sub;
   if (id >= (uint32_t)a.n_streams * nblk) return;
   const int stream = id / (uint32_t)nblk;  // of the launch
   const int blk = id - (uint32_t)stream * nblk;
@@ -640,10 +661,10 @@ __global__ __launch_bounds__(256, F32 ? 3 : 4) void compress_kernel(CompressArgs
   if (BITS == 16 || tail) {
     row_elements<D>(a, in_stream, tok0, tail ? a.n_stored - 1 : tok0 + 31, q, tg, e);
 #pragma unroll
-    for (int n = 0; n < 8; ++n) k.load(a.k, e[n], n);
+    for (int n = 0; n < 8; ++n) k.template load<kNt>(a.k, e[n], n);
     if constexpr (!F32) {
 #pragma unroll
-      for (int n = 0; n < 8; ++n) v.load(a.v, e[n], n);
+      for (int n = 0; n < 8; ++n) v.template load<kNt>(a.v, e[n], n);
     }
     const int ntok = tail ? a.n_stored - tok0 : 32;  // valid tokens of this block; zeros after them
     Rows<false> r;
@@ -653,7 +674,7 @@ __global__ __launch_bounds__(256, F32 ? 3 : 4) void compress_kernel(CompressArgs
     copy_out<D>(img, out, 64 * D, l);
     if constexpr (F32) {
 #pragma unroll
-      for (int n = 0; n < 8; ++n) v.load(a.v, e[n], n);
+      for (int n = 0; n < 8; ++n) v.template load<kNt>(a.v, e[n], n);
     }
 #pragma unroll
     for (int n = 0; n < 8; ++n) r.w[n] = row_token(n, tg) < ntok ? v.bf16(n) : u4v{0, 0, 0, 0};
@@ -664,17 +685,17 @@ __global__ __launch_bounds__(256, F32 ? 3 : 4) void compress_kernel(CompressArgs
   if constexpr (BITS != 16) {
     row_elements<D>(a, in_stream, tok0, tok0 + 31, q, tg, e);
 #pragma unroll
-    for (int n = 0; n < 8; ++n) k.load(a.k, e[n], n);
+    for (int n = 0; n < 8; ++n) k.template load<kNt>(a.k, e[n], n);
     if constexpr (!F32) {
 #pragma unroll
-      for (int n = 0; n < 8; ++n) v.load(a.v, e[n], n);
+      for (int n = 0; n < 8; ++n) v.template load<kNt>(a.v, e[n], n);
     }
     quant_keys<D, BITS, QS>(k, q, tg, img);
     if constexpr (F32) {  // not before: the keys' registers are needed
       __builtin_amdgcn_sched_barrier(0);
       row_elements<D>(a, in_stream, tok0, tok0 + 31, q, renewed(tg), e);
 #pragma unroll
-      for (int n = 0; n < 8; ++n) v.load(a.v, e[n], n);
+      for (int n = 0; n < 8; ++n) v.template load<kNt>(a.v, e[n], n);
     }
     quant_values<D, BITS, QS>(v, q, tg, img);
     copy_out<D>(img, out, quant_bytes<D, BITS, QS>(), l);
@@ -759,13 +780,13 @@ __global__ __launch_bounds__(256) void group_write_kernel(AppendArgs a) {
   if (tg == 3) {  // row 7 is token 31: the new one in place of a stale slot
     if (a.in_f32) {
       Rows<true> x;
-      x.load(a.k, e0, 0);
-      x.load(a.v, e0, 1);
+      x.load<false>(a.k, e0, 0);
+      x.load<false>(a.v, e0, 1);
       k.w[7] = x.bf16(0);
       v.w[7] = x.bf16(1);
     } else {
-      k.load(a.k, e0, 7);
-      v.load(a.v, e0, 7);
+      k.load<false>(a.k, e0, 7);
+      v.load<false>(a.v, e0, 7);
     }
   }
   uint8_t* img = img_all + (wave * L::kBlocks + sub) * kImg;
@@ -846,10 +867,14 @@ using namespace kvk;
 // One W1 launch over `nstreams` streams of the arguments' layout.
 template <int D, int BITS, int QS>
 static void launch_w1_kernel(const CompressArgs& a, hipStream_t stream) {
-  constexpr int per_wg = 4 * Lanes<D>::kBlocks;
-  const dim3 g((unsigned)(((int64_t)a.n_streams * (a.nbf + 1) + per_wg - 1) / per_wg)), b(256);
-  if (a.in_f32) hipLaunchKernelGGL((compress_kernel<D, BITS, QS, true>), g, b, 0, stream, a);
-  else hipLaunchKernelGGL((compress_kernel<D, BITS, QS, false>), g, b, 0, stream, a);
+  const auto launch = [&](auto f32) {
+    constexpr bool F32 = decltype(f32)::value;
+    constexpr int waves = kWriteWaves<D, BITS, F32>, per_wg = waves * Lanes<D>::kBlocks;
+    const unsigned grid = (unsigned)(((int64_t)a.n_streams * (a.nbf + 1) + per_wg - 1) / per_wg);
+    hipLaunchKernelGGL((compress_kernel<D, BITS, QS, F32>), dim3(grid), dim3(64 * waves), 0, stream, a);
+  };
+  if (a.in_f32) launch(std::true_type{});
+  else launch(std::false_type{});
 }
 template <int D, int QS>
 static bool launch_w1_bits(const CompressArgs& a, hipStream_t stream) {
