@@ -48,7 +48,7 @@ struct DecodeItem {
   int32_t q_layer0;      // first reading layer, relative to layer_begin
   int32_t geff;          // query rows: G * readers
   int32_t nsplit;
-  int32_t split_blocks;
+  int32_t split_blocks;  // full blocks per split, or minus the ring depth (see split_length)
   int32_t wave_begin;    // first wave of this item within the launch (a multiple of 4)
   int32_t ws_off;        // float offset of the item's partials
   int32_t nchp;          // waves per (stream, split): 16-row chunks, padded to 1, 2 or 4
@@ -646,15 +646,15 @@ __device__ __forceinline__ void load_query(const DecodeArgs& a, const DecodeItem
 // register allocation.
 template <int D, int BITS, int QS, int POL>
 __device__ __forceinline__ void run_unit(const DecodeArgs& a, const DecodeItem& it, int sidx, int split,
-                                         int chunk, uint32_t* lds, int lane) {
+                                         int split_blocks, int chunk, uint32_t* lds, int lane) {
   constexpr int NR = ring_depth<BITS>();
   constexpr int NM = D / 16;
   constexpr int NX = BITS == 16 ? 0 : (QS == kQsKivi ? D / 32 : (QS == kQsG64 ? D / 64 : 0));
   const int b = it.b0 + sidx / a.Hkv, kvh = sidx % a.Hkv;  // sidx: the item's own stream index
   const int i16 = lane & 15, kg = lane >> 4;
   const int row = 16 * chunk + i16;
-  const int k0 = split * it.split_blocks;
-  const int k1 = min(a.nbf, k0 + it.split_blocks);
+  const int k0 = split * split_blocks;
+  const int k1 = min(a.nbf, k0 + split_blocks);
   const uint8_t* stream = a.arena + it.region + (int64_t)sidx * it.stream_bytes;
   State<D> u;
   u.m = -INFINITY;
@@ -718,6 +718,16 @@ __device__ __forceinline__ void run_unit(const DecodeArgs& a, const DecodeItem& 
   }
 }
 
+// Full blocks per split of a per-sequence item over nbf stored blocks.  The list serves
+// every n_stored: a launch of one round fixes the number of splits and cuts what is
+// stored evenly, in whole ring passes (split_blocks is minus the ring depth); any other
+// fixes their length.
+__device__ __forceinline__ int split_length(int nbf, int nsplit, int split_blocks) {
+  if (split_blocks > 0) return split_blocks;
+  const int per = max(1, (nbf + nsplit - 1) / nsplit), nr = -split_blocks;
+  return (per + nr - 1) / nr * nr;
+}
+
 template <bool BATCHED>
 __device__ __forceinline__ const DecodeItem& item_at(const DecodeArgs& a, int i) {
   if constexpr (BATCHED) return a.items_dev[i];
@@ -768,25 +778,26 @@ __global__ __launch_bounds__(256, 2) void gqa_decode_kernel(DecodeArgs a) {
   if (unit >= it.nb * a.Hkv * it.nsplit || 16 * chunk >= it.geff) return;  // alignment padding
   const int split = unit % it.nsplit;
   const int sidx = unit / it.nsplit;  // (b - b0) * Hkv + kvh
+  const int len = BATCHED ? split_length(a.nbf, it.nsplit, it.split_blocks) : it.split_blocks;
   // Per-sequence lists are laid out for the capacity: a split past the stored
   // blocks holds nothing at this n_stored (the merge reads only the live ones).
-  if (BATCHED && split * it.split_blocks >= a.nbf) return;
+  if (BATCHED && split * len >= a.nbf) return;
   uint32_t* lds = lds_meta[wslot];
   // A stream read by one wave is streamed non-temporally; the waves of a stream read
   // by several row chunks read it through the caches (the later reads hit).
   if (it.nchp == 1) {
     switch (it.bits) {
-      case 16: run_unit<D, 16, QS, kStreamPolicy>(a, it, sidx, split, chunk, lds, lane); break;
-      case 8: run_unit<D, 8, QS, kStreamPolicy>(a, it, sidx, split, chunk, lds, lane); break;
-      case 4: run_unit<D, 4, QS, kStreamPolicy>(a, it, sidx, split, chunk, lds, lane); break;
-      default: run_unit<D, 2, QS, kStreamPolicy>(a, it, sidx, split, chunk, lds, lane); break;
+      case 16: run_unit<D, 16, QS, kStreamPolicy>(a, it, sidx, split, len, chunk, lds, lane); break;
+      case 8: run_unit<D, 8, QS, kStreamPolicy>(a, it, sidx, split, len, chunk, lds, lane); break;
+      case 4: run_unit<D, 4, QS, kStreamPolicy>(a, it, sidx, split, len, chunk, lds, lane); break;
+      default: run_unit<D, 2, QS, kStreamPolicy>(a, it, sidx, split, len, chunk, lds, lane); break;
     }
   } else {
     switch (it.bits) {
-      case 16: run_unit<D, 16, QS, 0>(a, it, sidx, split, chunk, lds, lane); break;
-      case 8: run_unit<D, 8, QS, 0>(a, it, sidx, split, chunk, lds, lane); break;
-      case 4: run_unit<D, 4, QS, 0>(a, it, sidx, split, chunk, lds, lane); break;
-      default: run_unit<D, 2, QS, 0>(a, it, sidx, split, chunk, lds, lane); break;
+      case 16: run_unit<D, 16, QS, 0>(a, it, sidx, split, len, chunk, lds, lane); break;
+      case 8: run_unit<D, 8, QS, 0>(a, it, sidx, split, len, chunk, lds, lane); break;
+      case 4: run_unit<D, 4, QS, 0>(a, it, sidx, split, len, chunk, lds, lane); break;
+      default: run_unit<D, 2, QS, 0>(a, it, sidx, split, len, chunk, lds, lane); break;
     }
   }
 }
@@ -823,7 +834,8 @@ __global__ __launch_bounds__(256) void gqa_combine_kernel(CombineArgs a) {
     const CombItem& ci = a.citems[item];
     nsplit = ci.nsplit, geff = ci.geff, ws_off = ci.ws_off, b0 = ci.b0, sbytes = ci.stream_bytes;
     tail_off = ci.tail;
-    nlive = min(nsplit, (a.nbf + ci.split_blocks - 1) / ci.split_blocks);
+    const int len = split_length(a.nbf, nsplit, ci.split_blocks);
+    nlive = min(nsplit, (a.nbf + len - 1) / len);
   } else {
     item = a.layer_item[li];
     slot = a.layer_slot0[li] + h % a.G;
@@ -1105,7 +1117,7 @@ kvk_status prepare(const kvk_table* t, int32_t l0, int32_t l1, const void* q, in
   ca.nbf = nbf;
   ca.map = nullptr;
 
-  const GqaSplitRule split_rule = gqa_split_rule(t, l0, l1);
+  const GqaSplitRule split_rule = gqa_split_rule(t, l0, l1, nbf_split);
   // One work item per distinct anchor read by the range (§2.1 depth sharing): per
   // anchor for all sequences, or per (sequence, anchor) under per-sequence plans.
   SmallVec<DecodeItem, kMaxItems> items;
@@ -1131,6 +1143,7 @@ kvk_status prepare(const kvk_table* t, int32_t l0, int32_t l1, const void* q, in
         it.geff = G * (re - rb);
         it.split_blocks = gqa_item_split_blocks(s, anc, l0, l1, nbf_split, split_rule);
         it.nsplit = n_splits(nbf_split, it.split_blocks);
+        if (batched && split_rule.round > 0) it.split_blocks = -ring_depth_for(it.bits);
         it.nchp = gqa_chunk_waves((it.geff + 15) / 16);
         it.b0 = b0;
         it.nb = nb;

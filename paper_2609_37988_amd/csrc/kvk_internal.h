@@ -105,15 +105,14 @@ constexpr int gqa_ring_depth(int bits) { return bits == 16 ? 2 : (bits == 8 ? 2 
 inline int32_t ring_depth_for(int32_t bits) { return gqa_ring_depth(bits); }
 
 // Blocks processed per split of the decode kernel for a `bits`-bit anchor whose
-// streams hold n_blocks full blocks.  *count_bound (if given) receives a bound of the
-// split count of every length up to n_blocks, so that a workspace sized with it at
-// the capacity covers every n_stored (the count itself is not monotone in the
+// streams hold n_blocks full blocks.  *count_bound (if given; byte rule) receives a bound
+// of the split count of every length up to n_blocks, so that a workspace sized with it
+// at the capacity covers every n_stored (the count itself is not monotone in the
 // length).  `waves` D1 waves read each split (an item's chunk waves), so its target
 // and its bounds are that many times the per-wave ones.
 struct GqaSplitRule {
-  int64_t bytes;   // cache bytes per D1 wave the launch aims at
-  int64_t round;   // > 0: a launch of one round of waves, its cost per wave (table.cpp)
-  int32_t nb_cap;  // full-block capacity of its streams
+  int64_t bytes;  // cache bytes per D1 wave the launch aims at (from the capacity)
+  int64_t round;  // > 0: a launch of one round of waves, its cost per wave (table.cpp)
 };
 int32_t split_blocks_for(int32_t bits, int32_t qscheme, int32_t head_dim, int32_t n_blocks, const GqaSplitRule& rule,
                          int32_t waves, int32_t* count_bound = nullptr);
@@ -125,9 +124,10 @@ constexpr int32_t gqa_chunk_waves(int32_t nch) { return nch == 1 ? 1 : (nch == 2
 // in table s (split_blocks_for with the item's chunk waves in one workgroup).
 int32_t gqa_item_split_blocks(const kvk_table* s, int32_t anchor, int32_t l0, int32_t l1, int32_t n_blocks,
                               const GqaSplitRule& rule, int32_t* count_bound = nullptr);
-// How a decode over layers [l0, l1) of a GQA table splits its streams; computed from
-// the capacity, so that the splits' partials are bounded for every n_stored.
-GqaSplitRule gqa_split_rule(const kvk_table* t, int32_t l0, int32_t l1);
+// How a decode over layers [l0, l1) of a GQA table splits its streams of n_blocks full
+// blocks: the stored ones, or the capacity under per-sequence plans, whose list serves
+// every n_stored.
+GqaSplitRule gqa_split_rule(const kvk_table* t, int32_t l0, int32_t l1, int32_t n_blocks);
 
 // Bytes at the head of the workspace that hold the device-side work list of a
 // decode over [l0, l1) of a per-sequence table (decode.hip).

@@ -87,9 +87,14 @@ static int64_t gqa_split_bytes(const kvk_table* t, int32_t l0, int32_t l1) {
 // in sixteenths of a 4-bit block's (7B and 14B stacks: about 3, 2.2, 2 and 2 us).
 static int32_t round_cost(int32_t bits) { return bits == 16 ? 24 : (bits == 8 ? 18 : 16); }
 
-// Full blocks per split in a one-round launch of cost `round` per wave: at least one
-// pass of the kernel's ring, and at most kRoundSplits splits per stream.
+// Full blocks per split in a one-round launch of cost `round` per wave over streams of
+// n_blocks: at least one pass of the kernel's ring, and at most kRoundSplits splits per
+// stream.
 constexpr int64_t kRoundWaves = 2048;  // D1 wave slots of an MI355X (256 CUs x 8 waves)
+// More splits than 64 shorten the waves of a long stream but lengthen its merge: one
+// layer at 7B, int4, device time: 131072 tokens, batch 1 72 us (128 splits: 46), 8192
+// tokens, bf16 13.2 (128: 17.1), batch 4, 16384 tokens, int4 21 (128: 28).  1 MiB and 128
+// KiB splits whatever the launch take 76, 52 and 40 us.
 constexpr int64_t kRoundSplits = 64;
 static int64_t round_target(int32_t bits, int64_t round, int64_t n_blocks) {
   const int64_t least = std::max<int64_t>(ring_depth_for(bits), (n_blocks + kRoundSplits - 1) / kRoundSplits);
@@ -104,21 +109,24 @@ static int32_t gqa_item_rows(const kvk_table* s, int32_t anchor, int32_t l0, int
   return G * (re - rb);
 }
 
-// The cost per wave of a launch that the byte rule would leave with fewer waves than
-// slots, 0 for any other launch.  Such a launch lasts as long as its longest wave, so
-// its streams are cut into splits of about equal time, as short as keeps every wave
-// in the first round (a wave more than the slots starts after a whole first wave has
-// ended).  Measured at batch 1, 7B shape, 4097 tokens, D1: bf16 whole streams 150 us,
-// 64-block splits 84, 16-block splits (896 waves) 39; int4 whole 127, 64 blocks 67, 8
-// blocks (1792 waves) 22; 14B shape, 8192 tokens, int8: 32-block splits (3072 waves)
-// 145 us, 48 (2304 waves) 162, 64 (1536) 147, whole 251; eight 7B sequences with their
-// own mixed plans, 6000 tokens: 64-block splits of every precision (1824 waves) 203 us
-// against 250 with the byte rule.  Launches that fill the slots keep the byte rule:
+// The cost per wave of a launch over streams of n_blocks that the byte rule would leave
+// with fewer waves than slots, 0 for any other launch.  Such a launch lasts as long as
+// its longest wave, so its streams are cut into splits of about equal time, as short as
+// keeps every wave in the first round (a wave more than the slots starts after a whole
+// first wave has ended).  n_blocks is what is stored, not the capacity: 7B int4, one
+// sequence of 4097 tokens, 31 us in a table of 4097, 32768 or 131072 tokens (with the
+// capacity's split length 31, 52 and 130).  Measured at batch 1, 7B shape, 4097 tokens,
+// D1: bf16 whole streams 150 us, 64-block splits 84, 16-block splits (896 waves) 39; int4
+// whole 127, 64 blocks 67, 8 blocks (1792 waves) 22; 14B shape, 8192 tokens, int8:
+// 32-block splits (3072 waves) 145 us, 48 (2304 waves) 162, 64 (1536) 147, whole 251; eight 7B
+// sequences with their own mixed plans, 6000 tokens: 64-block splits of every precision
+// (1824 waves) 203 us against 250 with the byte rule.  Launches that fill the slots keep the byte rule:
 // several rounds of waves balance themselves (128k eviction stack, 4700 waves: 1104 us
 // against 1138 in one round; 14B mixed stack at batch 8: 610 against 713).
-static int64_t gqa_round_cost(const kvk_table* t, int32_t l0, int32_t l1, const GqaSplitRule& bytes) {
-  const int64_t nb = t->nb_cap;
+static int64_t gqa_round_cost(const kvk_table* t, int32_t l0, int32_t l1, int32_t n_blocks, int64_t bytes) {
+  const int64_t nb = n_blocks;
   if (nb < 1) return 0;
+  const GqaSplitRule rule = {bytes, 0};
   int64_t units[4] = {0, 0, 0, 0};  // chunk waves over all streams, by precision
   int64_t byte_waves = 0;
   static constexpr int32_t kBits[4] = {16, 8, 4, 2};
@@ -134,7 +142,7 @@ static int64_t gqa_round_cost(const kvk_table* t, int32_t l0, int32_t l1, const 
                             gqa_chunk_waves((gqa_item_rows(s, a, l0, l1) + 15) / 16);
       for (int k = 0; k < 4; ++k)
         if (s->bits[a] == kBits[k]) units[k] += waves;
-      byte_waves += waves * n_splits((int32_t)nb, gqa_item_split_blocks(s, a, l0, l1, (int32_t)nb, bytes));
+      byte_waves += waves * n_splits(n_blocks, gqa_item_split_blocks(s, a, l0, l1, n_blocks, rule));
       if (byte_waves >= kRoundWaves) return 0;
     }
   }
@@ -150,35 +158,37 @@ static int64_t gqa_round_cost(const kvk_table* t, int32_t l0, int32_t l1, const 
   }
 }
 
-// Bytes of the split partials of a decode over [l0, l1) by a split rule: per query row
-// (layer, b, head) and split (o[d_h], m, l, 2 pad) in fp32, the splits of every
-// n_stored up to the capacity (full blocks; the merge kernel attends to the tail).
-static int64_t gqa_partial_bytes(const kvk_table* t, int32_t l0, int32_t l1, const GqaSplitRule& rule) {
+// Bytes of the split partials of a decode over [l0, l1) that cover every n_stored up to
+// the capacity: per query row (layer, b, head) and split (o[d_h], m, l, 2 pad) in fp32
+// (full blocks; the merge kernel attends to the tail).  Either the byte rule's splits of
+// the capacity, or a launch of one round: at most kRoundWaves waves of at most 16 rows,
+// and at most a split per ring pass of the capacity.  Both grow with the range, so that
+// the round's splits of a part fit a workspace of the whole.
+static int64_t gqa_partial_bytes(const kvk_table* t, int32_t l0, int32_t l1) {
   const int32_t G = t->d.n_q_heads / t->d.n_kv_heads;
   const size_t n_seq = t->seq.empty() ? 1 : t->seq.size();
-  int64_t floats = 0;
+  const GqaSplitRule rule = {gqa_split_bytes(t, l0, l1), 0};
+  int64_t by_bytes = 0, by_round = 0, rows = 0;  // in partials; rows of a wave
   for (size_t i = 0; i < n_seq; ++i) {
     const kvk_table* s = t->seq.empty() ? t : t->seq[i];
+    const int64_t n = (int64_t)s->d.batch * s->d.n_kv_heads * G;
     for (int l = l0; l < l1; ++l) {
+      const int32_t a = s->info.anchor_of[l], nr = ring_depth_for(s->bits[a]);
       int32_t bound = 0;
-      gqa_item_split_blocks(s, s->info.anchor_of[l], l0, l1, t->nb_cap, rule, &bound);
-      floats += (int64_t)s->d.batch * s->d.n_kv_heads * G * bound * (t->d.head_dim + 4);
+      gqa_item_split_blocks(s, a, l0, l1, t->nb_cap, rule, &bound);
+      by_bytes += n * bound;
+      by_round += n * std::max(1, (t->nb_cap + nr - 1) / nr);
+      rows = std::max<int64_t>(rows, std::min(16, gqa_item_rows(s, a, l0, l1)));
     }
   }
-  return round256(floats * (int64_t)sizeof(float));
+  const int64_t partials = std::max(by_bytes, std::min(by_round, rows * kRoundWaves));
+  return round256(partials * (t->d.head_dim + 4) * (int64_t)sizeof(float));
 }
 
-GqaSplitRule gqa_split_rule(const kvk_table* t, int32_t l0, int32_t l1) {
+GqaSplitRule gqa_split_rule(const kvk_table* t, int32_t l0, int32_t l1, int32_t n_blocks) {
   GqaSplitRule r;
-  r.nb_cap = t->nb_cap;
   r.bytes = gqa_split_bytes(t, l0, l1);
-  r.round = 0;
-  r.round = gqa_round_cost(t, l0, l1, r);
-  // A workspace of the whole range serves its parts: a part whose partials would need
-  // more keeps the byte rule.
-  if (r.round > 0 && (l0 > 0 || l1 < t->d.n_layers) &&
-      gqa_batched_list_bytes(t, l0, l1) + gqa_partial_bytes(t, l0, l1, r) > t->info.workspace_bytes)
-    r.round = 0;
+  r.round = gqa_round_cost(t, l0, l1, n_blocks, r.bytes);
   return r;
 }
 
@@ -187,9 +197,8 @@ int32_t split_blocks_for(int32_t bits, int32_t qscheme, int32_t head_dim, int32_
   const int64_t nr = ring_depth_for(bits);
   const int64_t nb = n_blocks > 0 ? n_blocks : 1;
   if (rule.round > 0) {  // a launch of one round: equal times per wave
-    const int64_t target = round_target(bits, rule.round, rule.nb_cap);
+    const int64_t target = round_target(bits, rule.round, nb);
     const int64_t nsplit = (nb + target - 1) / target;
-    if (count_bound) *count_bound = (int32_t)nsplit;  // grows with nb, as below
     return (int32_t)(((nb + nsplit - 1) / nsplit + nr - 1) / nr * nr);
   }
   int64_t target_bytes = rule.bytes;
@@ -584,7 +593,7 @@ extern "C" kvk_status kvk_workspace_bytes(const kvk_table* t, int32_t l0, int32_
     *out = total;
     return KVK_OK;
   }
-  *out = (size_t)(gqa_batched_list_bytes(t, l0, l1) + gqa_partial_bytes(t, l0, l1, gqa_split_rule(t, l0, l1)));
+  *out = (size_t)(gqa_batched_list_bytes(t, l0, l1) + gqa_partial_bytes(t, l0, l1));
   return KVK_OK;
 }
 

@@ -120,6 +120,29 @@ def test_batched_plans_match_oracle(qs):
             assert np.array_equal(kd[b].cpu().numpy(), Kr[0]) and np.array_equal(vd[b].cpu().numpy(), Vr[0])
 
 
+def test_batched_decode_far_below_the_capacity():
+    """One work list serves every n_stored: its splits cut what is stored evenly.  Capacity 8192 tokens; nothing,
+    a tail alone, a block and a token, fewer blocks than splits, more, and a length near the capacity."""
+    D, cap = 128, 8192
+    c = BatchCase(PLANS, 8, 2, D, cap)
+    Ks, Vs = _inputs(c, cap, 1180)
+    scale = 1.0 / np.sqrt(D)
+    q = synth.q_random(1181, c.L, c.B, 8, D)
+    for n in (0, 20, 33, 300, 2100, 8150):
+        say(f"case batched far below the capacity n={n}")
+        K, V = [x[:, :, :n].contiguous() for x in Ks], [x[:, :, :n].contiguous() for x in Vs]
+        if n:
+            for l in range(c.L):
+                kvk.compress_layer(c.table, l, K[l].to(DEV), V[l].to(DEV), n, None, c.arena)
+        out = c.decode(q, n, scale)
+        if not n:
+            assert not out.any()
+            continue
+        oarena = OC.compress_arena_batched(c.od, c.oplans, [x.float().numpy() for x in K], [x.float().numpy() for x in V])
+        ref = OC.decode_step_batched(c.od, c.oplans, oarena, q.float().numpy().astype(np.float64), n, scale)
+        assert rel_err(out, ref) <= TOL
+
+
 def test_write_of_more_sequences_than_one_launch_serves():
     """70 sequences with their own plans (layer 0 int4 in every plan: 70 sequences of
     one bit-width, more than the 64 one write launch serves; layer 1 int2 or bf16 by

@@ -267,6 +267,24 @@ def test_split_merge(bits, D, n):
     assert rel_err(out, ref) <= TOL
 
 
+@pytest.mark.parametrize("bits", [16, 8, 4, 2])
+def test_splits_follow_the_stored_length(bits):
+    """A launch that leaves the GPU part empty splits what is stored, whatever the capacity: the same splits,
+    so the same bits, in a table of 2017 tokens and in one of 64 times as many (whose 64-block splits would
+    hold the 63 stored blocks in one)."""
+    n = 2017
+    outs = []
+    for cap in (n, 64 * n):
+        say(f"case capacity bits={bits} cap={cap}")
+        c = Case(1, 4, 1, 128, 1, cap, [(0, bits)])
+        k, v = synth.kv_random(2200 + bits, 1, 1, n, 128)
+        c.compress(0, k.cuda(), v.cuda(), n)
+        outs.append(c.decode(synth.q_random(2201, 1, 1, 4, 128).cuda(), n, 0.09))
+    assert torch.equal(*outs)
+    ref = _oracle_out(c, {0: (_np(k), _np(v))}, synth.q_random(2201, 1, 1, 4, 128), n, 0.09)
+    assert rel_err(_np(outs[0]), ref) <= TOL
+
+
 def test_workspace_covers_every_stored_length():
     """The split count is not monotone in the stored length (rounding a split up to
     whole ring passes can save one: a 4-bit stream with 25-block splits takes 8 splits

@@ -492,3 +492,41 @@ def test_gqa_workspace_of_parts(L, B, hkv, G, T):
         part = kvk.workspace_bytes(t, l, l + 1)
         one = B * hkv * G * (D + 4) * 4
         assert one <= part <= max(whole, one * (T * 4 * D // (128 << 10) + 2))
+
+
+@pytest.mark.parametrize("L,B,hkv,G,T,mix", [(1, 1, 1, 4, 20000, (4,)), (28, 1, 4, 7, 8192, (16, 8, 4, 2)),
+                                             (3, 2, 8, 5, 40000, (2, 16, 8)), (48, 2, 8, 5, 4097, (16,)),
+                                             (6, 1, 2, 20, 9000, (4, 0, 0, 8, 2, 0))])
+def test_gqa_workspace_serves_every_length(L, B, hkv, G, T, mix):
+    """The split rule follows the stored length: at no length does a decode over the workspace's own range,
+    or over one layer of it, find the workspace too small (every call then stops at the dummy pointers)."""
+    plan = kvk.make_plan([(0, b) if b else (1, 16) for b in (mix[i % len(mix)] for i in range(L))])
+    t = kvk.layer_table(kvk.make_dims(kvk.GQA, L, hkv * G, hkv, 128, batch=B, max_tokens=T), plan)
+    f = ctypes.c_void_p(256)
+    whole = kvk.workspace_bytes(t, 0, L)
+    assert whole >= max(kvk.workspace_bytes(t, l, l + 1) for l in range(L))
+    for n in sorted({T} | set(range(37, T, 32 if L < 20 else 160))):
+        for l0, l1 in ((0, L), (L // 2, L // 2 + 1)):
+            for ws in {kvk.workspace_bytes(t, l0, l1), whole}:
+                _raw(kvk.ERR_INVALID, "kvk_decode_attention", t.handle, l0, l1, f, kvk.BF16, n, 0.1, None, None, f, f, f,
+                     ws, None)
+                assert "GPU-accessible" in kvk.last_error()
+
+
+def _splits(L, B, hq, hkv, bits, cap, n, l0=0, l1=None):
+    """Splits per stream of a decode at n tokens, from the workspace it asks for (plans of anchors alone)."""
+    t = kvk.layer_table(kvk.make_dims(kvk.GQA, L, hq, hkv, 128, batch=B, max_tokens=cap), kvk.make_plan([(0, bits)] * L))
+    f, l1 = ctypes.c_void_p(256), l1 or L
+    _raw(kvk.ERR_BUFFER, "kvk_decode_attention", t.handle, l0, l1, f, kvk.BF16, n, 0.1, None, None, f, f, f, 0, None)
+    need = int(re.search(r"< (\d+) needed", kvk.last_error()).group(1))
+    per, rest = divmod(need, (l1 - l0) * B * hq * 132 * 4)
+    assert rest == 0
+    return per
+
+
+@pytest.mark.parametrize("bits", [16, 8, 4, 2])
+def test_gqa_splits_follow_the_stored_length(bits):
+    """A decode that leaves the GPU part empty splits what is stored, whatever the table's capacity."""
+    for L, hq, hkv in ((1, 28, 4), (28, 28, 4), (48, 40, 8)):
+        assert len({_splits(L, 1, hq, hkv, bits, cap, 4097) for cap in (4097, 32768, 131072)}) == 1
+    assert _splits(1, 1, 28, 4, bits, 131072, 4097) >= 16
