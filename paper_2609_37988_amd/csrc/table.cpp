@@ -122,13 +122,21 @@ static int32_t gqa_item_rows(const kvk_table* s, int32_t anchor, int32_t l0, int
 // sequences with their own mixed plans, 6000 tokens: 64-block splits of every precision
 // (1824 waves) 203 us against 250 with the byte rule.  Launches that fill the slots keep the byte rule:
 // several rounds of waves balance themselves (128k eviction stack, 4700 waves: 1104 us
-// against 1138 in one round; 14B mixed stack at batch 8: 610 against 713).
+// against 1138 in one round; 14B mixed stack at batch 8: 610 against 713).  So do
+// launches of mostly bf16 items with at least kBf16Waves waves: those saturate HBM, and
+// more only disturb it (all bf16, 14B shape, batch 2, 8192 tokens, 768 whole streams:
+// 453 us, 1536 waves 487; 7B, batch 2, 8192 tokens, 672 waves: 143 us, 2016 waves 153;
+// 7B, batch 4, 4097 tokens, 896 waves: 155 us, 1792 waves 178; but 512 waves fill half of
+// the CUs: 8 layers at 14B, batch 8, 8192 tokens 363 us, 2048 waves 321).  Three
+// quarters of the items bf16 and the rest int4, 14B, batch 2, 8192 tokens: 402 us, in
+// one round 464; half of them, 4097 tokens: 254 us, in one round 178.
+constexpr int64_t kBf16Waves = 576;
 static int64_t gqa_round_cost(const kvk_table* t, int32_t l0, int32_t l1, int32_t n_blocks, int64_t bytes) {
   const int64_t nb = n_blocks;
   if (nb < 1) return 0;
   const GqaSplitRule rule = {bytes, 0};
   int64_t units[4] = {0, 0, 0, 0};  // chunk waves over all streams, by precision
-  int64_t byte_waves = 0;
+  int64_t byte_waves = 0, bf16_waves = 0;
   static constexpr int32_t kBits[4] = {16, 8, 4, 2};
   const size_t n_seq = t->seq.empty() ? 1 : t->seq.size();
   for (size_t i = 0; i < n_seq; ++i) {
@@ -142,10 +150,13 @@ static int64_t gqa_round_cost(const kvk_table* t, int32_t l0, int32_t l1, int32_
                             gqa_chunk_waves((gqa_item_rows(s, a, l0, l1) + 15) / 16);
       for (int k = 0; k < 4; ++k)
         if (s->bits[a] == kBits[k]) units[k] += waves;
-      byte_waves += waves * n_splits(n_blocks, gqa_item_split_blocks(s, a, l0, l1, n_blocks, rule));
+      const int64_t n = waves * n_splits(n_blocks, gqa_item_split_blocks(s, a, l0, l1, n_blocks, rule));
+      byte_waves += n;
+      if (s->bits[a] == 16) bf16_waves += n;
       if (byte_waves >= kRoundWaves) return 0;
     }
   }
+  if (bf16_waves >= kBf16Waves && units[0] >= 3 * (units[1] + units[2] + units[3])) return 0;
   int64_t cost = 0;
   for (int k = 0; k < 4; ++k) cost += units[k] * nb * round_cost(kBits[k]);
   for (int64_t round = std::max<int64_t>(cost / kRoundWaves, 1);; round += round / 16 + 1) {

@@ -530,3 +530,12 @@ def test_gqa_splits_follow_the_stored_length(bits):
     for L, hq, hkv in ((1, 28, 4), (28, 28, 4), (48, 40, 8)):
         assert len({_splits(L, 1, hq, hkv, bits, cap, 4097) for cap in (4097, 32768, 131072)}) == 1
     assert _splits(1, 1, 28, 4, bits, 131072, 4097) >= 16
+
+
+def test_gqa_splits_of_bf16_launches():
+    """Enough bf16 waves to saturate HBM (576) keep the byte rule; fewer are cut to fill one round."""
+    assert _splits(48, 2, 40, 8, 16, 8192, 8192) == 1   # 768 whole streams
+    assert _splits(28, 2, 28, 4, 16, 8192, 8192) == 3   # 672 waves
+    assert _splits(28, 4, 28, 4, 16, 4097, 4097) == 2   # 896 waves
+    assert _splits(8, 8, 40, 8, 16, 8192, 8192) == 4    # 512 whole streams would leave CUs idle
+    assert _splits(28, 1, 28, 4, 16, 4097, 4097) == 16  # 112 streams
