@@ -9,13 +9,13 @@
 // or as bf16 at b = 16 (§2.2: a b = 16 GQA layer is the uncompressed cache).
 // The layout written is the one documented in include/kvk.h.
 //
-// One wave writes one 32-token block of one stream at d_h 128, two at d_h 64 (half a
-// wave each), without barriers.  Lane (q, tg) holds channels 8q .. 8q+7 of the eight
+// One wave writes the keys or the values of one 32-token block of one stream at d_h 128,
+// of two at d_h 64 (half a wave each), without barriers.  Lane (q, tg) holds channels 8q .. 8q+7 of the eight
 // tokens 16 (n/4) + 4 tg + n%4, n = 0..7: its loads are 16 bytes and a row's lanes
 // read it whole, the 8 channels of a token are a chunk of the K layout and the 8
 // tokens of a channel a chunk of the V layout, so every code word is formed in one
 // lane's registers.  Group minima and maxima are in-lane trees finished by lane
-// swaps.  The block is put together in the wave's LDS slot, in its output order, and
+// swaps.  The part is put together in the wave's LDS slot, in its output order, and
 // leaves with 16-byte stores of contiguous kilobytes.  The kernel is specialised per
 // head width, bit-width, scheme and input type.
 #include <hip/hip_runtime.h>
@@ -113,7 +113,8 @@ struct Rows<false> {
     return __uint_as_float(c & 1 ? x & 0xffff0000u : x << 16);
   }
   __device__ __forceinline__ u4v bf16(int n) const { return w[n]; }
-  // Forget the conversions of an earlier pass over the rows (64 registers if kept).
+  // Forget the conversions of an earlier pass over the rows (64 registers if kept), or
+  // keep the common ones of two branches in each.
   __device__ __forceinline__ void renew() {
 #pragma unroll
     for (int n = 0; n < 8; ++n)
@@ -270,8 +271,8 @@ __device__ __forceinline__ void store_chunk(uint8_t* part, int at, const uint32_
   }
 }
 
-// Byte of the K chunk (token t, channels 8q..8q+7) and of the V chunk (channel c, token
-// set tg) in the code parts of a block, by the share layout of kvk.h.
+// Byte of the K chunk (token t, channels 8q..8q+7) in the K codes of a block and of the V
+// chunk (channel c, token set tg) in its V codes, by the share layout of kvk.h.
 template <int D, int BITS>
 __device__ __forceinline__ int k_chunk_byte(int t, int q) {
   const int j = q >> 2, lam = 16 * (q & 3) + (t & 15), tile = 2 * D * BITS * (t >> 4);
@@ -283,8 +284,8 @@ template <int D, int BITS>
 __device__ __forceinline__ int v_chunk_byte(int c, int tg) {
   const int m = c >> 4, lam = 16 * tg + (c & 15);
   constexpr int P = D * BITS / 16;
-  if constexpr (BITS == 2) return 4 * D * BITS + share_byte(P, lam, 4 * (m >> 1)) + (m & 1);
-  return 4 * D * BITS + share_byte(P, lam, BITS * m);
+  if constexpr (BITS == 2) return share_byte(P, lam, 4 * (m >> 1)) + (m & 1);
+  return share_byte(P, lam, BITS * m);
 }
 
 // Reduction over the token sets of one channel's minimum or maximum, all lanes ending
@@ -447,11 +448,12 @@ __device__ __forceinline__ u4v high_halves(const uint32_t (&x)[8]) {
   return r;
 }
 
-// Keys (codes and metadata) of a block into its LDS image.
+// Keys of a block into their LDS image: the codes, then the metadata.
 template <int D, int BITS, int QS, class R>
 __device__ __forceinline__ void quant_keys(R& rows, int q, int tg, uint8_t* img) {
   tg = renewed(tg);
-  uint8_t* meta = img + 8 * D * BITS;
+  rows.renew();
+  uint8_t* meta = img + 4 * D * BITS;
   float s[8], y[8], z[8];
   if constexpr (QS == kQsKivi) {
     kivi_key_groups<D, BITS>(rows, q, tg, reinterpret_cast<uint16_t*>(meta), s, y, z);
@@ -492,11 +494,12 @@ __device__ __forceinline__ void quant_keys(R& rows, int q, int tg, uint8_t* img)
   }
 }
 
-// Values of a block into its LDS image.
+// Values of a block, likewise.
 template <int D, int BITS, int QS, class R>
 __device__ __forceinline__ void quant_values(R& rows, int q, int tg, uint8_t* img) {
   tg = renewed(tg);
-  uint8_t* meta = img + 8 * D * BITS;
+  rows.renew();
+  uint8_t* meta = img + 4 * D * BITS;
   if constexpr (QS == kQsSym) {
     Row r[8];
 #pragma unroll
@@ -504,7 +507,7 @@ __device__ __forceinline__ void quant_values(R& rows, int q, int tg, uint8_t* im
       float am = amax8([&](int c) { return rows.get(n, c); });
       am = D == 128 ? max16(am) : max8(am);
       r[n] = make_row<BITS>(am);
-      if (q == 0) reinterpret_cast<uint16_t*>(meta)[32 + row_token(n, tg)] = r[n].bits;
+      if (q == 0) reinterpret_cast<uint16_t*>(meta)[row_token(n, tg)] = r[n].bits;
     }
     rows.renew();
     __builtin_amdgcn_sched_barrier(0);
@@ -522,7 +525,7 @@ __device__ __forceinline__ void quant_values(R& rows, int q, int tg, uint8_t* im
     uint32_t sz[8];
     token_groups<BITS, GL>(rows, q, s, y, z, sz);
     if (q % GL == 0) {  // fp16 index ((g*2 + w)*4 + kg)*8 + s
-      u4v* m4 = reinterpret_cast<u4v*>(meta + (QS == kQsKivi ? 4 * D : 2 * D)) + 8 * (q / GL) + tg;
+      u4v* m4 = reinterpret_cast<u4v*>(meta) + 8 * (q / GL) + tg;
       m4[0] = low_halves(sz);
       m4[4] = high_halves(sz);
     }
@@ -572,23 +575,33 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// The first `bytes` of an LDS image to global memory, by the lanes of the block.
-template <int D>
-__device__ __forceinline__ void copy_out(const uint8_t* img, uint8_t* out, int bytes, int l) {
-  wave_lds_fence();
-  for (int o = 16 * l; o < bytes; o += 16 * Lanes<D>::kPerBlock)
-    __builtin_nontemporal_store(*reinterpret_cast<const u4v*>(img + o), reinterpret_cast<u4v*>(out + o));
-  wave_lds_fence();
-}
+// Bytes of the K (or V) codes and of the K (or V) metadata of a quantised block, which
+// holds K codes, V codes, K metadata, V metadata; and of the LDS image of a part.
+template <int D, int BITS>
+constexpr int kCodeBytes = 4 * D * BITS;
+template <int D, int QS>
+constexpr int kMetaBytes = QS == kQsKivi ? 4 * D : (QS == kQsSym ? 64 : 2 * D);
+template <int D, int BITS, int QS>
+constexpr int kImageBytes =
+    BITS == 16 || kCodeBytes<D, BITS> + kMetaBytes<D, QS> < 64 * D ? 64 * D : kCodeBytes<D, BITS> + kMetaBytes<D, QS>;
 
-// Bytes of a quantised block, and of the LDS image of a block.
-template <int D, int BITS, int QS>
-constexpr int quant_bytes() {
-  return QS == kQsKivi ? 8 * D * (BITS + 1) : QS == kQsSym ? 8 * D * BITS + 128 : 8 * D * BITS + 4 * D;
+// The LDS image of part `part` (0 K, 1 V) to its places in the block at `out`, by the
+// lanes of the block: a bf16 part, or codes and metadata.
+template <int D>
+__device__ __forceinline__ void copy_bf16_part(const uint8_t* img, uint8_t* out, int part, int l) {
+  wave_lds_fence();
+  for (int o = 16 * l; o < 64 * D; o += 16 * Lanes<D>::kPerBlock)
+    __builtin_nontemporal_store(*reinterpret_cast<const u4v*>(img + o),
+                                reinterpret_cast<u4v*>(out + 64 * D * part + o));
 }
 template <int D, int BITS, int QS>
-constexpr int image_bytes() {
-  return BITS == 16 || quant_bytes<D, BITS, QS>() < 64 * D ? 64 * D : quant_bytes<D, BITS, QS>();
+__device__ __forceinline__ void copy_quant_part(const uint8_t* img, uint8_t* out, int part, int l) {
+  constexpr int cb = kCodeBytes<D, BITS>, mb = kMetaBytes<D, QS>;
+  wave_lds_fence();
+  for (int o = 16 * l; o < cb + mb; o += 16 * Lanes<D>::kPerBlock) {
+    const int to = o < cb ? cb * part + o : 2 * cb + mb * part + (o - cb);
+    __builtin_nontemporal_store(*reinterpret_cast<const u4v*>(img + o), reinterpret_cast<u4v*>(out + to));
+  }
 }
 
 // The input elements of a lane's rows: stored tokens tok0 .. (none past `last`), through
@@ -613,15 +626,19 @@ __device__ __forceinline__ void row_elements(const CompressArgs& a, int in_strea
   for (int n = 0; n < 8; ++n) e[n] = ((int64_t)in_stream * a.n_tokens + pos[n]) * D + 8 * q;
 }
 
-// Waves of a workgroup.  One at d_h 64 for fp32 inputs and for copies, whose launches are
-// short and last as long as their fullest CU (4 x 8 KV heads x 8192 tokens, fp32 inputs,
-// int8: 36.3 -> 33.9 us; bf16 copy 27.3 -> 26.3; but quantised bf16 inputs 22.3 -> 23.2).
-template <int D, int BITS, bool F32>
-constexpr int kWriteWaves = D == 64 && (F32 || BITS == 16) ? 1 : 4;
+// Waves of a workgroup.  One: a launch of few blocks spreads over the CUs, and a short one
+// lasts as long as its fullest CU (one token of 8 KV heads, d_h 128: 2.5 us; two waves
+// 2.8, four 3.6; 4 x 4 KV heads x 2000 tokens of d_h 64, int8: 6.0, 7.4 and 8.5).  Two for
+// bf16 rows at d_h 128: 4 x 8 KV heads x 8192 tokens, int8, 35.9 us, with one 37.0.
+template <int D, bool F32>
+constexpr int kWriteWaves = D == 128 && !F32 ? 2 : 1;
 
-// One wave writes one 32-token block of one stream (two at d_h 64), with BITS-bit codes
-// (or bf16 at BITS = 16; a stream's tail block is always bf16).  The keys' and values'
-// loads are all issued first for bf16 inputs (16 KiB in flight per wave).
+// One wave writes the keys or the values of one 32-token block of one stream (two at d_h
+// 64), with BITS-bit codes (or bf16 at BITS = 16; a stream's tail block is always bf16).
+// Not both in one wave: its chain of loads, codes and stores is what a small launch takes
+// (8 KV heads x 256 tokens, d_h 128, int8: 6.1 -> 4.1 us; d_h 64 7.5 -> 5.5), and the
+// registers of one part leave room for as many loads in flight on a full GPU (14B mixed
+// stack, 32 anchors: 1150 -> 1121 us).
 //
 // Bound: HBM and the vector units about equally (d_h 128, KIVI32: about 14 vector
 // operations per value; the input is read and the codes are written once).
@@ -630,17 +647,18 @@ constexpr int kWriteWaves = D == 64 && (F32 || BITS == 16) ? 1 : 4;
 // -> 1170 us), not where they are copied: inputs still in the last-level cache take 41.5 us
 // at d_h 128 (4 x 8 KV heads x 8192 tokens) against 45.7, others 49.3 against 47.7.
 template <int D, int BITS, int QS, bool F32>
-__global__ __launch_bounds__((64 * kWriteWaves<D, BITS, F32>), F32 ? 3 : 4) void compress_kernel(CompressArgs a) {
+__global__ __launch_bounds__((64 * kWriteWaves<D, F32>), F32 ? 3 : 4) void compress_kernel(CompressArgs a) {
   using L = Lanes<D>;
-  constexpr int kWaves = kWriteWaves<D, BITS, F32>;
+  constexpr int kWaves = kWriteWaves<D, F32>;
   constexpr bool kNt = !F32 && BITS != 16;
-  constexpr int kImg = image_bytes<D, BITS, QS>();
+  constexpr int kImg = kImageBytes<D, BITS, QS>;
   __shared__ __align__(16) uint8_t img_all[kWaves * L::kBlocks * kImg];
 
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l = lane % L::kPerBlock, q = l % L::kQ, tg = l / L::kQ, sub = lane / L::kPerBlock;
   const int nblk = a.nbf + 1;
-  const uint32_t id = (blockIdx.x * kWaves + wave) * L::kBlocks + sub;
+  const uint32_t gw = blockIdx.x * kWaves + wave, id = (gw >> 1) * L::kBlocks + sub;
+  const int part = gw & 1;  // 0: keys, 1: values
   if (id >= (uint32_t)a.n_streams * nblk) return;
   const int stream = id / (uint32_t)nblk;  // of the launch
   const int blk = id - (uint32_t)stream * nblk;
@@ -656,49 +674,29 @@ __global__ __launch_bounds__((64 * kWriteWaves<D, BITS, F32>), F32 ? 3 : 4) void
 
   uint8_t* img = img_all + (wave * L::kBlocks + sub) * kImg;
   uint8_t* out = sbase + (tail ? (int64_t)a.nb_cap * a.block_bytes : (int64_t)blk * a.block_bytes);
-  Rows<F32> k, v;
+  const void* in = part ? a.v : a.k;
+  Rows<F32> rows;
   int64_t e[8];
   if (BITS == 16 || tail) {
     row_elements<D>(a, in_stream, tok0, tail ? a.n_stored - 1 : tok0 + 31, q, tg, e);
 #pragma unroll
-    for (int n = 0; n < 8; ++n) k.template load<kNt>(a.k, e[n], n);
-    if constexpr (!F32) {
-#pragma unroll
-      for (int n = 0; n < 8; ++n) v.template load<kNt>(a.v, e[n], n);
-    }
+    for (int n = 0; n < 8; ++n) rows.template load<kNt>(in, e[n], n);
     const int ntok = tail ? a.n_stored - tok0 : 32;  // valid tokens of this block; zeros after them
     Rows<false> r;
 #pragma unroll
-    for (int n = 0; n < 8; ++n) r.w[n] = row_token(n, tg) < ntok ? k.bf16(n) : u4v{0, 0, 0, 0};
-    bf16_keys<D>(r, q, tg, img);
-    copy_out<D>(img, out, 64 * D, l);
-    if constexpr (F32) {
-#pragma unroll
-      for (int n = 0; n < 8; ++n) v.template load<kNt>(a.v, e[n], n);
-    }
-#pragma unroll
-    for (int n = 0; n < 8; ++n) r.w[n] = row_token(n, tg) < ntok ? v.bf16(n) : u4v{0, 0, 0, 0};
-    bf16_values<D>(r, q, tg, img);
-    copy_out<D>(img, out + 64 * D, 64 * D, l);
+    for (int n = 0; n < 8; ++n) r.w[n] = row_token(n, tg) < ntok ? rows.bf16(n) : u4v{0, 0, 0, 0};
+    if (part == 0) bf16_keys<D>(r, q, tg, img);
+    else bf16_values<D>(r, q, tg, img);
+    copy_bf16_part<D>(img, out, part, l);
     return;
   }
   if constexpr (BITS != 16) {
     row_elements<D>(a, in_stream, tok0, tok0 + 31, q, tg, e);
 #pragma unroll
-    for (int n = 0; n < 8; ++n) k.template load<kNt>(a.k, e[n], n);
-    if constexpr (!F32) {
-#pragma unroll
-      for (int n = 0; n < 8; ++n) v.template load<kNt>(a.v, e[n], n);
-    }
-    quant_keys<D, BITS, QS>(k, q, tg, img);
-    if constexpr (F32) {  // not before: the keys' registers are needed
-      __builtin_amdgcn_sched_barrier(0);
-      row_elements<D>(a, in_stream, tok0, tok0 + 31, q, renewed(tg), e);
-#pragma unroll
-      for (int n = 0; n < 8; ++n) v.template load<kNt>(a.v, e[n], n);
-    }
-    quant_values<D, BITS, QS>(v, q, tg, img);
-    copy_out<D>(img, out, quant_bytes<D, BITS, QS>(), l);
+    for (int n = 0; n < 8; ++n) rows.template load<kNt>(in, e[n], n);
+    if (part == 0) quant_keys<D, BITS, QS>(rows, q, tg, img);
+    else quant_values<D, BITS, QS>(rows, q, tg, img);
+    copy_quant_part<D, BITS, QS>(img, out, part, l);
   }
 }
 
@@ -747,62 +745,65 @@ __global__ __launch_bounds__(256) void tail_write_kernel(AppendArgs a) {
   *reinterpret_cast<uint16_t*>(tailb + v_bf16_byte(D, t, c)) = new_token_bf16(a.v, e, a.in_f32);
 }
 
-// The token that fills the tail (pos % 32 == 31) completes a 32-token group: one wave
-// (half a wave at d_h 64) per (stream, anchor) quantises the tail's bf16 values plus
-// the new token (rounded to bf16) into full block pos / 32, exactly as the prefill
-// write quantises a block.  The tail is then empty (its stale slots are never read).
+// The token that fills the tail (pos % 32 == 31) completes a 32-token group: a wave for
+// the keys and one for the values of each (stream, anchor), of two streams at d_h 64,
+// quantise the tail's bf16 values plus the new token (rounded to bf16) into full block
+// pos / 32, exactly as the prefill write quantises a block.  The tail is then empty (its
+// stale slots are never read).
 template <int D, int QS>
-__global__ __launch_bounds__(256) void group_write_kernel(AppendArgs a) {
+__global__ __launch_bounds__(128) void group_write_kernel(AppendArgs a) {
   using L = Lanes<D>;
-  constexpr int kImg = image_bytes<D, 8, QS>();
-  __shared__ __align__(16) uint8_t img_all[4 * L::kBlocks * kImg];
+  constexpr int kImg = kImageBytes<D, 8, QS>;
+  __shared__ __align__(16) uint8_t img_all[2 * L::kBlocks * kImg];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l = lane % L::kPerBlock, q = l % L::kQ, tg = l / L::kQ, sub = lane / L::kPerBlock;
-  const int sidx = (blockIdx.x * 4 + wave) * L::kBlocks + sub;
+  const int part = wave;  // 0: keys, 1: values
+  const int sidx = blockIdx.x * L::kBlocks + sub;
   if (sidx >= a.n_streams) return;
   const AppendItem& it = a.items[blockIdx.y];
   uint8_t* base = a.arena + it.region + (int64_t)sidx * it.stream_bytes;
   const uint8_t* tailb = base + (int64_t)a.nb_cap * it.block_bytes;
   const int64_t e0 = (int64_t)it.row * a.row_stride + (int64_t)(it.s0 + sidx) * D + 8 * q;
   // the tail block's pieces are the lane's rows (K) and its channels' tokens (V)
-  Rows<false> k, v;
-  u4v vc[8];
+  Rows<false> rows;
+  if (part == 0) {
 #pragma unroll
-  for (int n = 0; n < 8; ++n) {
-    k.w[n] = *reinterpret_cast<const u4v*>(tailb + k_bf16_byte(D, row_token(n, tg), 8 * q));
-    vc[n] = *reinterpret_cast<const u4v*>(tailb + 64 * D + share_byte(D, 16 * tg + ((8 * q + n) & 15), q >> 1 << 4));
+    for (int n = 0; n < 8; ++n)
+      rows.w[n] = *reinterpret_cast<const u4v*>(tailb + k_bf16_byte(D, row_token(n, tg), 8 * q));
+  } else {
+    u4v vc[8];
+#pragma unroll
+    for (int n = 0; n < 8; ++n)
+      vc[n] = *reinterpret_cast<const u4v*>(tailb + 64 * D + share_byte(D, 16 * tg + ((8 * q + n) & 15), q >> 1 << 4));
+#pragma unroll
+    for (int n = 0; n < 8; ++n)
+#pragma unroll
+      for (int p = 0; p < 4; ++p)
+        rows.w[n][p] = __builtin_amdgcn_perm(vc[2 * p + 1][n >> 1], vc[2 * p][n >> 1], n & 1 ? 0x07060302u : 0x05040100u);
   }
-#pragma unroll
-  for (int n = 0; n < 8; ++n)
-#pragma unroll
-    for (int p = 0; p < 4; ++p)
-      v.w[n][p] = __builtin_amdgcn_perm(vc[2 * p + 1][n >> 1], vc[2 * p][n >> 1], n & 1 ? 0x07060302u : 0x05040100u);
   if (tg == 3) {  // row 7 is token 31: the new one in place of a stale slot
+    const void* in = part ? a.v : a.k;
     if (a.in_f32) {
       Rows<true> x;
-      x.load<false>(a.k, e0, 0);
-      x.load<false>(a.v, e0, 1);
-      k.w[7] = x.bf16(0);
-      v.w[7] = x.bf16(1);
+      x.load<false>(in, e0, 0);
+      rows.w[7] = x.bf16(0);
     } else {
-      k.load<false>(a.k, e0, 7);
-      v.load<false>(a.v, e0, 7);
+      rows.load<false>(in, e0, 7);
     }
   }
   uint8_t* img = img_all + (wave * L::kBlocks + sub) * kImg;
   uint8_t* out = base + (int64_t)(a.pos >> 5) * it.block_bytes;
   if (it.bits == 16) {
-    bf16_keys<D>(k, q, tg, img);
-    copy_out<D>(img, out, 64 * D, l);
-    bf16_values<D>(v, q, tg, img);
-    copy_out<D>(img, out + 64 * D, 64 * D, l);
+    if (part == 0) bf16_keys<D>(rows, q, tg, img);
+    else bf16_values<D>(rows, q, tg, img);
+    copy_bf16_part<D>(img, out, part, l);
     return;
   }
 #define KVK_GROUP_BITS(B) \
   { \
-    quant_keys<D, B, QS>(k, q, tg, img); \
-    quant_values<D, B, QS>(v, q, tg, img); \
-    copy_out<D>(img, out, quant_bytes<D, B, QS>(), l); \
+    if (part == 0) quant_keys<D, B, QS>(rows, q, tg, img); \
+    else quant_values<D, B, QS>(rows, q, tg, img); \
+    copy_quant_part<D, B, QS>(img, out, part, l); \
   }
   if (it.bits == 8) KVK_GROUP_BITS(8)
   else if (it.bits == 4) KVK_GROUP_BITS(4)
@@ -869,8 +870,9 @@ template <int D, int BITS, int QS>
 static void launch_w1_kernel(const CompressArgs& a, hipStream_t stream) {
   const auto launch = [&](auto f32) {
     constexpr bool F32 = decltype(f32)::value;
-    constexpr int waves = kWriteWaves<D, BITS, F32>, per_wg = waves * Lanes<D>::kBlocks;
-    const unsigned grid = (unsigned)(((int64_t)a.n_streams * (a.nbf + 1) + per_wg - 1) / per_wg);
+    constexpr int waves = kWriteWaves<D, F32>, blocks = Lanes<D>::kBlocks;
+    const int64_t all = 2 * (((int64_t)a.n_streams * (a.nbf + 1) + blocks - 1) / blocks);  // keys and values
+    const unsigned grid = (unsigned)((all + waves - 1) / waves);
     hipLaunchKernelGGL((compress_kernel<D, BITS, QS, F32>), dim3(grid), dim3(64 * waves), 0, stream, a);
   };
   if (a.in_f32) launch(std::true_type{});
@@ -1091,16 +1093,16 @@ static kvk_status append_gqa(const kvk_table* t, int32_t l0, int32_t l1, const v
       if (d.head_dim == 128) hipLaunchKernelGGL(tail_write_kernel<128>, g3, b3, 0, stream, a);
       else hipLaunchKernelGGL(tail_write_kernel<64>, g3, b3, 0, stream, a);
     } else {
-      const int per_wg = d.head_dim == 128 ? 4 : 8;  // streams of a workgroup
-      const dim3 g3((unsigned)((a.n_streams + per_wg - 1) / per_wg), (unsigned)n);
+      const int per_wg = d.head_dim == 128 ? 1 : 2;  // streams of a workgroup
+      const dim3 g3((unsigned)((a.n_streams + per_wg - 1) / per_wg), (unsigned)n), b2(128);
       if (d.head_dim == 128) {
-        if (qs == KVK_Q_KIVI32) hipLaunchKernelGGL((group_write_kernel<128, kQsKivi>), g3, b3, 0, stream, a);
-        else if (qs == KVK_Q_GROUP64) hipLaunchKernelGGL((group_write_kernel<128, kQsG64>), g3, b3, 0, stream, a);
-        else hipLaunchKernelGGL((group_write_kernel<128, kQsSym>), g3, b3, 0, stream, a);
+        if (qs == KVK_Q_KIVI32) hipLaunchKernelGGL((group_write_kernel<128, kQsKivi>), g3, b2, 0, stream, a);
+        else if (qs == KVK_Q_GROUP64) hipLaunchKernelGGL((group_write_kernel<128, kQsG64>), g3, b2, 0, stream, a);
+        else hipLaunchKernelGGL((group_write_kernel<128, kQsSym>), g3, b2, 0, stream, a);
       } else {
-        if (qs == KVK_Q_KIVI32) hipLaunchKernelGGL((group_write_kernel<64, kQsKivi>), g3, b3, 0, stream, a);
-        else if (qs == KVK_Q_GROUP64) hipLaunchKernelGGL((group_write_kernel<64, kQsG64>), g3, b3, 0, stream, a);
-        else hipLaunchKernelGGL((group_write_kernel<64, kQsSym>), g3, b3, 0, stream, a);
+        if (qs == KVK_Q_KIVI32) hipLaunchKernelGGL((group_write_kernel<64, kQsKivi>), g3, b2, 0, stream, a);
+        else if (qs == KVK_Q_GROUP64) hipLaunchKernelGGL((group_write_kernel<64, kQsG64>), g3, b2, 0, stream, a);
+        else hipLaunchKernelGGL((group_write_kernel<64, kQsSym>), g3, b2, 0, stream, a);
       }
     }
     const hipError_t e = hipGetLastError();

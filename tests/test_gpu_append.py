@@ -174,3 +174,28 @@ def test_mla_append_matches_oracle_and_decodes(qs):
     err = rel_err(out, ref)
     say(f"  max|diff| / max|out| = {err:.2e}")
     assert err <= TOL
+
+
+@pytest.mark.parametrize("qs", [kvk.KIVI32, kvk.SYMROW, kvk.GROUP64], ids=["kivi32", "symrow", "group64"])
+@pytest.mark.parametrize("D,Hkv", [(64, 1), (64, 3), (128, 3)])
+def test_flush_and_write_of_odd_stream_counts(qs, D, Hkv):
+    """A wave of the flush and of the prefill write takes one part of two blocks at d_h 64: with an odd number of
+    them the last one's other half stays idle.  Four layers (every bit-width), 61 tokens prefilled (two blocks
+    and a tail a stream) and three appended (a flush), against the prefill write of all 64."""
+    say(f"case odd streams qs={qs} D={D} Hkv={Hkv}")
+    plan, n = [(0, b) for b in (16, 8, 4, 2)], 64
+    a, b = (Case(4, 2 * Hkv, Hkv, D, 1, n, plan, qscheme=qs) for _ in range(2))
+    kv = [synth.kv_random(330 + l, 1, Hkv, n, D) for l in range(4)]
+    for l, (k, v) in enumerate(kv):
+        a.compress(l, k.to(DEV), v.to(DEV), n)
+        b.compress(l, k[:, :, :n - 3].to(DEV), v[:, :, :n - 3].to(DEV), n - 3)
+    for t in range(n - 3, n):
+        kvk.append_token(b.table, 0, 4, torch.stack([k[:, :, t] for k, _ in kv]).to(DEV),
+                         torch.stack([v[:, :, t] for _, v in kv]).to(DEV), t, b.arena)
+    for l in range(4):
+        for h in range(Hkv):
+            want = OC.compress_stream(a.odims, plan[l][1], _np(kv[l][0])[0, h], _np(kv[l][1])[0, h])
+            for c in (a, b):
+                got, _, _ = _gqa_valid(c.odims, plan[l][1], c.stream_bytes_host(l, 0, h), n)
+                ref, _, _ = _gqa_valid(c.odims, plan[l][1], want, n)
+                assert np.array_equal(got, ref), f"layer {l}, head {h}"
