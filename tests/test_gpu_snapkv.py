@@ -23,14 +23,14 @@ pytestmark = pytest.mark.gpu
 W = 32
 
 
-def _run(B, Hq, Hkv, D, n, keep, seed, zero_keys=False):
+def _run(B, Hq, Hkv, D, n, keep, seed, zero_keys=False, sign=1.0):
     G = Hq // Hkv
     case = Case(1, Hq, Hkv, D, B, n, [(0, 4)], keep=keep)
     k, _ = synth.kv_random(seed, B, Hkv, n, D)
     if zero_keys:
         k = torch.zeros_like(k)
     q = synth.q_random(seed + 1, B, Hq, W, D)  # [B, Hq, 32, D]
-    scale = 1.0 / np.sqrt(D)
+    scale = sign / np.sqrt(D)
     keep_out = torch.full((B, Hkv, keep), -1, dtype=torch.int32, device=DEV)
     imp = torch.empty((B, Hkv, n), dtype=torch.float32, device=DEV)
     ws = torch.empty(kvk.snapkv_workspace_bytes(case.table, n), dtype=torch.uint8, device=DEV)
@@ -63,15 +63,32 @@ def _check(B, Hkv, n, keep, keep_gpu, imp_gpu, kn, qn, scale):
 
 
 @pytest.mark.parametrize("Hq,Hkv,D,n,keep", [
-    (10, 2, 128, 300, 150),     # G 5 (the 14B group), ragged length, one chunk
-    (10, 2, 128, 4500, 1125),   # three chunks, keep 1/4
-    (8, 1, 128, 2100, 263),     # G 8 (the widest), chunk boundary just past 2048
+    # 128-token chunks, in which a wave takes one step of 32 tokens
+    (10, 2, 128, 300, 150),     # G 5 (the 14B group), ragged length, three chunks
+    (10, 2, 128, 4500, 1125),   # 36 chunks, keep 1/4
+    (8, 1, 128, 2100, 263),     # G 8 (the widest), a last chunk of 52 tokens
     (4, 4, 64, 777, 400),       # G 1, d_h 64
 ])
 def test_snapkv_matches_oracle(Hq, Hkv, D, n, keep):
     say(f"case snapkv Hq={Hq} Hkv={Hkv} D={D} n={n} keep={keep}")
     B = 2
     case, k, q, scale, keep_gpu, imp_gpu, kn, qn = _run(B, Hq, Hkv, D, n, keep, 700 + n)
+    _check(B, Hkv, n, keep, keep_gpu, imp_gpu, kn, qn, scale)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,D,n,keep,sign", [
+    (8, 8, 8, 64, 2100, 700, 1.0),     # 384-token chunks: three steps a wave, the last chunk 180 tokens
+    (8, 40, 8, 128, 2100, 525, 1.0),   # the same at G 5, d_h 128
+    (8, 64, 8, 128, 2080, 300, -1.0),  # G 8, whole waves in the last chunk, a negative scale
+    (8, 16, 8, 64, 3000, 1000, -1.0),  # G 2, the window inside a chunk's last steps
+    (32, 8, 8, 64, 4100, 1000, 1.0),   # 2048-token chunks: 16 steps a wave, the last chunk 4 tokens
+])
+def test_snapkv_steps_of_a_wave(B, Hq, Hkv, D, n, keep, sign):
+    """Enough streams that a workgroup's chunk is longer than one step of its waves: the running maximum
+    and sum are rescaled from step to step, the next keys are read ahead, and the masked steps follow."""
+    say(f"case snapkv steps B={B} Hq={Hq} Hkv={Hkv} D={D} n={n} keep={keep} sign={sign}")
+    assert n * B * Hkv > 65536
+    case, k, q, scale, keep_gpu, imp_gpu, kn, qn = _run(B, Hq, Hkv, D, n, keep, 740 + n + Hq, sign=sign)
     _check(B, Hkv, n, keep, keep_gpu, imp_gpu, kn, qn, scale)
 
 
