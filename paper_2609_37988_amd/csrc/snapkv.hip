@@ -58,8 +58,11 @@ __device__ __forceinline__ f4 mfma_bf16(bf16x8 a, bf16x8 b, f4 c) {
 // query rows): lane (row i16, kg) holds tokens 4 kg .. 4 kg + 3 of its row, so a row's
 // running maximum and sum are one register each and eight scores share one rescale.
 // Bound: about evenly the exponentials (four cycles each per SIMD lane group), the
-// products and, for long prompts, the key reads.  B 4 x 8 KV heads x 131072 positions,
-// 5 heads a group: see snapkv_select's figures at launch_scores.
+// products and, for long prompts, the key reads.  The keys are read with plain loads, so
+// that what the last-level cache holds of them serves the second pass (8 KV heads x
+// 131072 positions of d_h 64, one head a group: 76 us a call, non-temporal 89; 4 x 8 KV
+// heads at d_h 128, 5 heads a group, 512 and 523).  Three workgroups per CU where their
+// queries and records fit LDS together (d_h 128: up to 5 heads a group), two above.
 template <int D, int PASS, int G>
 __global__ __launch_bounds__(256, G <= 5 ? 3 : 2) void snap_scores_kernel(SnapArgs a) {
   constexpr int RT = 2 * G;  // row tiles of 16
@@ -108,7 +111,7 @@ __global__ __launch_bounds__(256, G <= 5 ? 3 : 2) void snap_scores_kernel(SnapAr
     for (int u = 0; u < 2; ++u) {
       const u4v* kp = reinterpret_cast<const u4v*>(kb + (int64_t)min(tt + 16 * u + i16, t1 - 1) * D);
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) kn[u][j] = bitcast<bf16x8>(__builtin_nontemporal_load(kp + 4 * j));
+      for (int j = 0; j < NJ; ++j) kn[u][j] = bitcast<bf16x8>(kp[4 * j]);
     }
   };
   // One step over the 32 tokens from tt: MASK where some row does not see all of them.
