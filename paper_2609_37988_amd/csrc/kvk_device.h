@@ -219,16 +219,6 @@ __host__ __device__ inline int64_t block_bytes(int D, int bits, int kivi) {
 __host__ __device__ inline int share_byte(int P, int lam, int o) {
   return P > 16 ? 1024 * (o >> 4) + 16 * lam + (o & 15) : lam * P + o;
 }
-// Inverse: the lane and share byte held at byte b of a part.
-__host__ __device__ inline void share_of(int P, int b, int& lam, int& o) {
-  if (P > 16) {
-    lam = (b & 1023) >> 4;
-    o = 16 * (b >> 10) + (b & 15);
-  } else {
-    lam = b / P;
-    o = b % P;
-  }
-}
 
 // Bit address of the K code of (token t, channel c) in a quantised block.
 __device__ __forceinline__ int64_t k_code_bit(int D, int bits, int t, int c) {

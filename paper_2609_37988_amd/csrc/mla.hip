@@ -352,9 +352,10 @@ struct ProjectedRows {
 // traffic that feeds them above.  Measured per layer, 16 x 8192 tokens of width 2048
 // under the profiler (before: 32-wide steps, loads one step ahead that all waves wait
 // for at one place): d = 64 121 us (4.5 TB/s of hidden rows), 128 137, 256 194, 512
-// 277-339 us (1.0 PFLOP/s at the shorter); the four layers 1061 -> 720 us per pass.  d =
-// 1024 from 5120-wide rows, 2 x 8192 tokens: 537 -> 281 us; 1000 tokens at d = 512: 77 ->
-// 64 us; 3 x 300 tokens at d = 128: 45 -> 27 us.
+// 277-339 us (1.0 PFLOP/s at the shorter); the four layers 1036 -> 750 us per pass.  d =
+// 1024 from 5120-wide rows, 2 x 8192 tokens: 537 -> 281 us (its waves fill the register
+// file: 21 to 23 registers, 88 to 96 bytes a lane, are spilled); 1000 tokens at d = 512: 77
+// -> 64 us; 3 x 300 tokens at d = 128: 45 -> 27 us.
 template <int D>
 struct ProjGeo {
   static constexpr int TOK = D > 512 ? 64 : 128;

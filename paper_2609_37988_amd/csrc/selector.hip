@@ -259,8 +259,9 @@ __global__ __launch_bounds__(256) void sel_rmsnorm_kernel(const float* x, const 
 //
 // The exponentials and the products take turns within a wave (a tile's chain is
 // scores, maximum, probabilities, product), so it is the waves of a SIMD that overlap
-// them: three (168 registers) instead of two (8192 tokens: 112 -> 107 us with the keys
-// in three splits instead of two).
+// them: three (168 registers, ten more spilled: 44 bytes a lane) instead of two (8192
+// tokens: 112 -> 107 us with the keys in three splits instead of two; 32768 tokens, whole
+// prompts 3336 -> 3067).
 __global__ __launch_bounds__(256, 3) void sel_attention_kernel(const uint16_t* qk, const uint16_t* vt, int vt_pitch,
                                                             uint16_t* out, int T, int key_len, float* part) {
   constexpr int KT = 64;
@@ -564,8 +565,10 @@ int64_t sel_attn_reserve(int T) {
 // Key splits of the attention: as many as make the 128-query workgroups' rounds over
 // the 768 places (three per CU) the shortest, each split at least 256 keys, a multiple
 // of 64, their records within `room` bytes; no empty split.  A further split has to
-// save 5 % of the time, for its records and their merge.  Returns the split count;
-// *key_len gets the keys per split.
+// save 5 % of the time, for its records and their merge.  The room follows the count that
+// two workgroups per CU would take (sel_attn_reserve), so a long prompt gets fewer than
+// the rounds ask for: one at 20000 tokens (a round; six would take 0.83), one at 32768 (two;
+// three would take 1.33).  Returns the split count; *key_len gets the keys per split.
 int sel_attn_splits(int T, int64_t room, int* key_len) {
   const int wgs = (T + 127) / 128 * kHeads;
   const int cap = (int)std::min<int64_t>(std::min(T / 256, 16), room / ((int64_t)T * kHeads * kRec * 4));
