@@ -287,10 +287,10 @@ def test_splits_follow_the_stored_length(bits):
 
 def test_workspace_covers_every_stored_length():
     """The split count is not monotone in the stored length (rounding a split up to
-    whole ring passes can save one: a 4-bit stream with 25-block splits takes 8 splits
-    at 190 blocks and 7 at 193), so the workspace sized at the capacity (193 blocks)
-    holds the partials of every shorter length: 190 blocks + 5 tail tokens decode
-    without a workspace error and match the oracle."""
+    whole ring passes can save one), so the workspace sized at the capacity (193
+    blocks) holds the partials of every shorter length: 190 blocks + 5 tail tokens
+    (one stream: a launch of one round) decode without a workspace error and match the
+    oracle."""
     say("case workspace bound gqa")
     cap, n = 193 * 32, 190 * 32 + 5
     c = Case(1, 4, 1, 128, 1, cap, [(0, 4)])
